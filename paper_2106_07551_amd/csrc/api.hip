@@ -833,7 +833,7 @@ static malib_status launch_rollout(malib_pop_t pop, const malib_env_desc* env, i
     const int n_agents = env->n_agents;
     const int64_t ns = plan.ns;
     const bool mlp = plan.mlp, persist = plan.persist;
-    ea.WT = b.wt;
+    ea.WP = b.wt;
     ea.obs = plan.bf16_obs ? b.obs : nullptr;
     if (traj) {
         ea.tr.act = traj->actions;
@@ -864,7 +864,7 @@ static malib_status launch_rollout(malib_pop_t pop, const malib_env_desc* env, i
                               b.tile_off, b.tile_info, pop->dev_flags, s));
     HIP_TRY(launch_reset(ea, n_envs, seed, env_offset, cur, done, s));
     if (env->kind == MALIB_ENV_FEATURE)
-        HIP_TRY(launch_transpose(env->W, b.wt, env->d, s));
+        HIP_TRY(launch_pack_dynamics(env->W, b.wt, env->d, s));
     pend(pi);
     if (trace && mlp) {
         if (trace->perm)

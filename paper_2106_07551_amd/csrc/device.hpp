@@ -123,37 +123,37 @@ __device__ __forceinline__ float exp_ref(float x)
 // (tanh x - x)/x^3 through the x^19 term; 0.55 <= |x| <= 9.01 ->
 // sign(x) (1 - 2/(exp_ref(2|x|) + 1)); |x| > 9.01 -> sign(x); NaN and signed
 // zeros unchanged.
+//
+// Straight-line: both formulas, then selects (a wavefront's lanes nearly always
+// take both sides of the branches, and exec-mask handling cost more than the
+// shorter side saves).  The large side is 1 - 2 / b with b = exp_ref(2|x|) + 1
+// in [4, 2^26]: 2 / b rounded is twice the rounded reciprocal y of b, obtained
+// from the hardware estimate (1 ulp) by one fused Newton step, and 1 - 2y is
+// formed with one rounding, as 1 - (2 / b) is.  |x| above 9.01 is replaced by
+// 9.5, where the formula gives 1 exactly.  The small side has x's
+// sign already; copysign serves both sides and keeps -0.  (Equal to the branched
+// form with the IEEE quotient for every one of the 2^32 fp32 inputs, checked
+// exhaustively on the device.)
 __device__ __forceinline__ float tanh_ref(float x)
 {
-    if (__builtin_isnan(x) || x == 0.0f)
-        return x;
-    float ax = __builtin_fabsf(x);
-    if (ax > 9.01f)
-        return __builtin_copysignf(1.0f, x);
-    if (ax < 0.55f) {
-        float y = x * x;
-        float p = -0x1.f57d78p-13f;
-        p = __builtin_fmaf(p, y, 0x1.355824p-11f);
-        p = __builtin_fmaf(p, y, -0x1.7da364p-10f);
-        p = __builtin_fmaf(p, y, 0x1.d6d3dp-9f);
-        p = __builtin_fmaf(p, y, -0x1.226e36p-7f);
-        p = __builtin_fmaf(p, y, 0x1.664f48p-6f);
-        p = __builtin_fmaf(p, y, -0x1.ba1ba2p-5f);
-        p = __builtin_fmaf(p, y, 0x1.111112p-3f);
-        p = __builtin_fmaf(p, y, -0x1.555556p-2f);
-        float x3 = x * y;
-        return __builtin_fmaf(x3, p, x);
-    }
-    // 1 - 2 / b with b = exp_ref(2|x|) + 1 in [4, 2^26]: 2 / b rounded is
-    // twice the rounded reciprocal y of b, obtained from the hardware estimate
-    // (1 ulp) by one fused Newton step, and 1 - 2y is formed with one rounding,
-    // as 1 - (2 / b) is.  (The result equals that of the IEEE quotient for
-    // every one of the 2^32 fp32 inputs, checked exhaustively on the device.)
-    const float b = exp_ref(2.0f * ax) + 1.0f;
+    const float ax = __builtin_fabsf(x);
+    const float y2 = x * x;
+    float p = -0x1.f57d78p-13f;
+    p = __builtin_fmaf(p, y2, 0x1.355824p-11f);
+    p = __builtin_fmaf(p, y2, -0x1.7da364p-10f);
+    p = __builtin_fmaf(p, y2, 0x1.d6d3dp-9f);
+    p = __builtin_fmaf(p, y2, -0x1.226e36p-7f);
+    p = __builtin_fmaf(p, y2, 0x1.664f48p-6f);
+    p = __builtin_fmaf(p, y2, -0x1.ba1ba2p-5f);
+    p = __builtin_fmaf(p, y2, 0x1.111112p-3f);
+    p = __builtin_fmaf(p, y2, -0x1.555556p-2f);
+    const float small = __builtin_fmaf(x * y2, p, x);
+    const float b = exp_ref(2.0f * (ax > 9.01f ? 9.5f : ax)) + 1.0f;
     float y = __builtin_amdgcn_rcpf(b);
     y = __builtin_fmaf(__builtin_fmaf(-b, y, 1.0f), y, y);
-    const float t = __builtin_fmaf(-2.0f, y, 1.0f);
-    return __builtin_copysignf(t, x);
+    const float large = __builtin_fmaf(-2.0f, y, 1.0f);
+    const float t = __builtin_copysignf(ax < 0.55f ? small : large, x);
+    return x != x ? x : t;
 }
 
 // Device error flags (bit values of malib_eval_stats.device_flags).

@@ -177,7 +177,7 @@ struct EnvArgs {
     uint32_t team_col;   // bit k set: seat k is on the column side (team -1)
     const float* Amat;
     const float* W;
-    const float* WT;     // transposed W (scratch)
+    const float* WP;     // W packed as MFMA operands (scratch)
     const float* emb;
     const float* u;
     // FEATURE with bf16 policies: the observation bf16_rne(s) of every env,
@@ -190,7 +190,7 @@ struct EnvArgs {
 hipError_t launch_zero_f32(float* x, int64_t n, hipStream_t s);
 hipError_t launch_reset(const EnvArgs& e, int64_t n_envs, uint64_t seed, int64_t env_offset,
                         void* state, uint8_t* done, hipStream_t s);
-hipError_t launch_transpose(const float* W, float* WT, int d, hipStream_t s);
+hipError_t launch_pack_dynamics(const float* W, float* WP, int d, hipStream_t s);
 hipError_t launch_env_step(const EnvArgs& e, const SampleArgs& sa, int64_t n_envs,
                            const void* state_in, void* state_out, uint8_t* done, float* ret,
                            unsigned long long* frames, hipStream_t s);

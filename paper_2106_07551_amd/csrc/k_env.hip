@@ -110,22 +110,23 @@ hipError_t launch_reset(const EnvArgs& e, int64_t n_envs, uint64_t seed, int64_t
     return hipGetLastError();
 }
 
-__global__ void transpose_kernel(const float* __restrict__ W, float* __restrict__ WT, int d)
+// W [d][d] -> the A operands of v_mfma_f32_16x16x4_f32, lane by lane:
+// WP[nt][g][lane][j] = W[16 nt + lane % 16][16 g + 4 j + lane / 16], so a lane
+// loads its operands of four consecutive k-steps (16 inputs) as 16 bytes and a
+// wavefront 1 KiB contiguous.
+__global__ void pack_dynamics_kernel(const float* __restrict__ W, float* __restrict__ WP, int d)
 {
-    __shared__ float tile[32][33];
-    int bx = blockIdx.x * 32, by = blockIdx.y * 32;
-    int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;   // 32 x 8
-    for (int r = ty; r < 32; r += 8)
-        tile[r][tx] = W[(int64_t)(by + r) * d + bx + tx];
-    __syncthreads();
-    for (int r = ty; r < 32; r += 8)
-        WT[(int64_t)(bx + r) * d + by + tx] = tile[tx][r];
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= d * d)
+        return;
+    const int j = i & 3, lane = (i >> 2) & 63, r = i >> 8, gs = d / 16;
+    const int nt = r / gs, g = r - nt * gs;
+    WP[i] = W[(16 * nt + (lane & 15)) * d + 16 * g + 4 * j + (lane >> 4)];
 }
 
-hipError_t launch_transpose(const float* W, float* WT, int d, hipStream_t s)
+hipError_t launch_pack_dynamics(const float* W, float* WP, int d, hipStream_t s)
 {
-    dim3 grid(d / 32, d / 32);
-    transpose_kernel<<<grid, 256, 0, s>>>(W, WT, d);
+    pack_dynamics_kernel<<<(d * d + 255) / 256, 256, 0, s>>>(W, WP, d);
     return hipGetLastError();
 }
 
@@ -259,23 +260,6 @@ __global__ __launch_bounds__(256) void step_pursuit_kernel(
 
 // ------------------------------------------------------------ feature dynamics
 
-// One workgroup of kFeatWaves wavefronts owns kFeatWaves*EPT envs and all D
-// outputs of each:
-//   s'[e][k] = tanh_ref( fma-chain_{c=0..D-1}(W[k][c], s[e][c]) + emb[0][a_0][k]
-//                        + emb[1][a_1][k] + ... )
-// Thread (tx = tid%64, ty = tid/64) keeps the accumulators of envs
-// ty*EPT..ty*EPT+EPT-1 and outputs g*64*GW + GW*tx + j (groups of GW <= 4
-// consecutive outputs); the input index c runs in ascending order through
-// LDS-staged chunks of WT (c-major) and of the state (so every accumulator
-// sees exactly the sequential fused chain, no split of the sum).  The reward
-// r = u . s' is then a sequential fused chain per env over the staged s'.
-constexpr int kFeatKC = 32;
-// Eight wavefronts per workgroup: the WT chunks staged through LDS serve twice
-// as many envs as with four, and the grid has half as many workgroups to ramp
-// up and drain (d=256: 50 vs 54 us per step of 16384 envs; d=512: -3%).
-constexpr int kFeatWaves = 8, kFeatThreads = 64 * kFeatWaves;
-
-// EPT envs per thread (8, 4, 2 or 1).
 // GW consecutive floats (GW = 1, 2 or 4) as one load or store: outputs are
 // mapped to threads in groups of GW consecutive indices, so the WT reads from
 // LDS, the embedding loads and the state stores are single wide accesses.
@@ -336,241 +320,414 @@ __device__ __forceinline__ void store_bf16(uint16_t* p, const FVec<GW>& t)
     }
 }
 
-template <int D, int EPT>
-__global__ __launch_bounds__(kFeatThreads) void step_feature_kernel(
-    const float* __restrict__ WT, const float* __restrict__ emb, const float* __restrict__ u,
-    EnvArgs ea, SampleArgs sa, int64_t n, const float* __restrict__ s_in,
-    float* __restrict__ s_out, float* __restrict__ ret)
+// Feature dynamics, for every env e and output k:
+//   s'[e][k] = tanh_ref( fma-chain_{c=0..D-1}(W[k][c], s[e][c]) + emb[0][a_0][k]
+//                        + emb[1][a_1][k] + ... )
+// then the reward r = u . s', a sequential fused chain per env.
+//
+// The chains run on the matrix cores: v_mfma_f32_16x16x4_f32 adds its four
+// products to the accumulator one after the other in ascending k, each as a
+// fused multiply-add with one rounding (compared bit for bit with a VALU chain,
+// subnormals, infinities and NaN included), so an accumulator that starts at 0
+// and takes the inputs in ascending order holds exactly the sequential fused
+// chain.  A = W (16 outputs x 4 inputs, packed by pack_dynamics_kernel and read
+// from the L2, 1 KiB per wavefront for 16 inputs), B = the state (4 inputs x 16
+// envs) from LDS, where the 16 inputs of a group sit in the operand order (input
+// 4 j + m at 4 m + j), so a lane reads its operands of four k-steps as 16 bytes.
+//
+// A tile is E = 16 RT envs.  Its accumulators go through LDS to one wavefront
+// per env, lane tx taking groups of GW consecutive outputs, so that the
+// embedding rows are read and the state rows written as whole lines.
+//
+// Bound: fp32 MFMA and VALU instructions share a SIMD's cycles (wavefronts doing
+// the one and the other take the sum of their times: 126 + 215 -> 334 us
+// measured), so the time is the chains at 157 TFLOP/s plus the VALU work, about
+// 50 instructions per output, mostly tanh_ref.  A fused-multiply-add chain on
+// the VALU takes twice the chains' time: d = 512, 65536 envs, 2 seats 486 ->
+// 311 us (110 TFLOP/s; MFMA 65% and VALU 20% of the cycles); d = 256, 16384
+// envs, 8 seats 44 -> 35 us (half of it the state's 42 MB and latencies).
+// Splitting the wavefronts into MFMA and epilogue ones with the next tile's
+// loads in flight gains nothing for that reason (389 and 44 us).
+template <int D, int RT, int WAVES>
+struct FeatTile {
+    static constexpr int E = 16 * RT;
+    static constexpr int KG = D / 16;               // groups of 16 inputs
+    static constexpr int NTW = D / 16 / WAVES;      // output tiles per wavefront
+    static constexpr int EPW = E / WAVES;           // envs per wavefront in the epilogue
+    static constexpr int NJ = D / 64;               // outputs per lane and env in the epilogue
+    static constexpr int GW = NJ < 4 ? NJ : 4;      // ... in groups of GW consecutive ones
+    static constexpr int NG = NJ / GW;              // output k of (g, j) = g*64*GW + GW*tx + j
+    static constexpr int SLD = D + 4;               // env row stride in LDS (rows 4 banks apart)
+    static constexpr int Q4 = D / 4;
+    static constexpr int SQ = E * Q4 / (64 * WAVES);   // state float4s per thread
+    static_assert(NTW * WAVES * 16 == D && EPW * WAVES == E && SQ * 64 * WAVES == E * Q4, "split");
+};
+
+typedef float v4f_t __attribute__((ext_vector_type(4)));
+
+struct FeatArgs {
+    const float* WP;
+    const float* emb;
+    const float* u;
+    EnvArgs ea;
+    SampleArgs sa;
+    int64_t n;
+    const float* s_in;
+    float* s_out;
+    float* ret;
+};
+
+// The tile's state rows -> registers (envs past the end: zeros, never stored).
+template <class T>
+__device__ __forceinline__ void feat_load_state(const FeatArgs& f, int64_t e0, int st,
+                                                int threads, v4f_t (&sreg)[T::SQ])
 {
-    constexpr int kFeatEnvs = kFeatWaves * EPT;
-    constexpr int NJ = D / 64;                  // outputs per thread
-    constexpr int GW = NJ < 4 ? NJ : 4;         // ... in groups of GW consecutive ones
-    constexpr int NG = NJ / GW;                 // output k of (group g, j) = g*64*GW + GW*tx + j
-    constexpr int SSTR = kFeatEnvs + 4;
-    constexpr int SLD = D + 4;                  // row stride of s' in LDS (16-byte rows)
-    constexpr int WS_FLOATS = kFeatKC * D > kFeatEnvs * SLD ? kFeatKC * D : kFeatEnvs * SLD;
-    __shared__ __attribute__((aligned(16))) float Ws[WS_FLOATS];
-    __shared__ __attribute__((aligned(16))) float Ss[kFeatKC * SSTR];
-    // the reward weights u, staged once: the chain then reads both of its
-    // operands from LDS (in-order returns, so its loads can run ahead)
-    __shared__ __attribute__((aligned(16))) float Us[D];
-    const int tid = threadIdx.x, tx = tid & 63, ty = tid >> 6;
-    const int64_t e0 = (int64_t)blockIdx.x * kFeatEnvs;
-    for (int k = tid; k < D; k += kFeatThreads)   // read after the main loop's barriers
-        Us[k] = u[k];
-
-    // Staging: chunk c0 of WT (KC x D floats, c-major) and of the state (32 envs
-    // x KC) goes global -> registers -> LDS; the loads of chunk c0+KC are issued
-    // before the FMAs of chunk c0 so their latency overlaps the arithmetic.
-    constexpr int WQ = kFeatKC * D / 4 / kFeatThreads;   // float4 of WT per thread per chunk
-    // state chunk: kFeatEnvs envs x KC columns = kFeatEnvs*8 float4; threads
-    // beyond that re-load env 0's chunk and skip the LDS store
-    const int el_ld = (tid >> 3) % kFeatEnvs, cq_ld = tid & 7;
-    const bool s_owner = (tid >> 3) < kFeatEnvs;
-    const int64_t e_ld = e0 + el_ld;
-    typedef float v4f __attribute__((ext_vector_type(4)));
-    const v4f* wsrc = reinterpret_cast<const v4f*>(WT) + tid;
-    const float* ssrc = s_in + (e_ld < n ? e_ld : 0) * D + cq_ld * 4;
-    v4f wreg[WQ];
-    v4f sreg;
 #pragma unroll
-    for (int q = 0; q < WQ; ++q)
-        wreg[q] = wsrc[q * kFeatThreads];
-    sreg = *reinterpret_cast<const v4f*>(ssrc);
+    for (int q = 0; q < T::SQ; ++q) {
+        const int i = q * threads + st, el = i / T::Q4, c4 = i - el * T::Q4;
+        sreg[q] = v4f_t{0.f, 0.f, 0.f, 0.f};
+        if (e0 + el < f.n)
+            sreg[q] = *reinterpret_cast<const v4f_t*>(f.s_in + (e0 + el) * (4 * T::Q4) + 4 * c4);
+    }
+}
 
-    // the actions of the workgroup's slots while the first chunk loads are in
-    // flight: one thread per slot, Gumbel-max over its logits, or the action
-    // the policy kernel sampled (envs past the end take action 0 and are never
-    // stored)
-    __shared__ __attribute__((aligned(8))) uint8_t act_s[kFeatEnvs * kMaxAgents];
-    if (tid < kFeatEnvs * ea.n_agents) {
-        const int el = tid / ea.n_agents, seat = tid - el * ea.n_agents;
-        const int64_t e = e0 + el;
-        int a = 0;
-        if (e < n) {
-            const int64_t slot = e * ea.n_agents + seat;
-            if (sa.actions) {
-                a = sa.actions[slot];   // sampled by the policy kernel
-            } else {
-                bool nan;
-                a = gumbel_action<kMaxActions>(sa.logits + slot * ea.A, ea.A, sa.seed,
-                                                (uint64_t)(sa.env_offset + e), sa.t, seat, nan);
-                if (nan)
-                    atomicOr(sa.flags, kErrNaN);
+// Trajectory observation of the step: bf16(s) of the staged rows.
+template <class T>
+__device__ __forceinline__ void feat_record_obs(const FeatArgs& f, int64_t e0, int st,
+                                                int threads, const v4f_t (&sreg)[T::SQ])
+{
+    const TrajArgs& tr = f.ea.tr;
+    if (!tr.obs)
+        return;
+    const int64_t rec0 = traj_rec(tr, f.sa.t, f.n, e0);
+#pragma unroll
+    for (int q = 0; q < T::SQ; ++q) {
+        const int i = q * threads + st, el = i / T::Q4, c4 = i - el * T::Q4;
+        int64_t rec = rec0 + el;
+        if (rec >= tr.cap)
+            rec %= tr.cap;
+        if (e0 + el < f.n)
+            *reinterpret_cast<uint2*>((uint16_t*)tr.obs + rec * (4 * T::Q4) + 4 * c4) =
+                make_uint2(pack_bf16x2(sreg[q].x, sreg[q].y), pack_bf16x2(sreg[q].z, sreg[q].w));
+    }
+}
+
+// The staged rows -> LDS in operand order.
+template <class T>
+__device__ __forceinline__ void feat_stage_state(float* Ss, int st, int threads,
+                                                 const v4f_t (&sreg)[T::SQ])
+{
+#pragma unroll
+    for (int q = 0; q < T::SQ; ++q) {
+        const int i = q * threads + st, el = i / T::Q4, c4 = i - el * T::Q4;
+        float* dst = Ss + el * T::SLD + (c4 >> 2) * 16 + (c4 & 3);
+        dst[0] = sreg[q].x;
+        dst[4] = sreg[q].y;
+        dst[8] = sreg[q].z;
+        dst[12] = sreg[q].w;
+    }
+}
+
+// W operands through a buffer resource: base and size in scalar registers, one
+// lane offset for all loads, the (wave-uniform) operand block's offset in a
+// scalar register, so the main loop spends no VALU on addresses (VALU and fp32
+// MFMA share a SIMD's cycles).
+using WSrc = __amdgpu_buffer_rsrc_t;
+
+__device__ __forceinline__ v4f_t load_w4(WSrc src, int blk, int loff)
+{
+    return __builtin_bit_cast(v4f_t,
+                              __builtin_amdgcn_raw_buffer_load_b128(src, loff, blk * 1024, 0));
+}
+
+// The chains of wavefront mw's output tiles over the staged state; the ring
+// holds groups 0 .. DEPTH-1 on entry.
+template <class T, int RT, int DEPTH>
+__device__ __forceinline__ void feat_mfma(WSrc W, const float* Ss, int mw, int tx,
+                                          v4f_t (&a)[DEPTH][T::NTW], v4f_t (&acc)[T::NTW][RT])
+{
+    static_assert(T::KG % DEPTH == 0, "whole rounds of the ring");
+#pragma unroll
+    for (int i = 0; i < T::NTW; ++i)
+#pragma unroll
+        for (int r = 0; r < RT; ++r)
+            acc[i][r] = v4f_t{0.f, 0.f, 0.f, 0.f};
+    const float* bp = Ss + (tx & 15) * T::SLD + 4 * (tx >> 4);
+#pragma unroll 1
+    for (int g0 = 0; g0 < T::KG; g0 += DEPTH) {
+#pragma unroll
+        for (int h = 0; h < DEPTH; ++h) {
+            const int g = g0 + h;
+            v4f_t b[RT];
+#pragma unroll
+            for (int r = 0; r < RT; ++r)
+                b[r] = *reinterpret_cast<const v4f_t*>(bp + 16 * r * T::SLD + 16 * g);
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int i = 0; i < T::NTW; ++i)
+#pragma unroll
+                    for (int r = 0; r < RT; ++r)
+                        acc[i][r] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[h][i][j], b[r][j],
+                                                                         acc[i][r], 0, 0, 0);
+            if constexpr (DEPTH < T::KG) {
+                // (past the end: a block of the next output tile, or zeros, unused)
+#pragma unroll
+                for (int i = 0; i < T::NTW; ++i)
+                    a[h][i] = load_w4(W, (mw * T::NTW + i) * T::KG + g + DEPTH, tx * 16);
             }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+}
+
+// Accumulators -> Ss[env][k] (lane: env tx % 16 of its row tile, 4 outputs).
+template <class T, int RT>
+__device__ __forceinline__ void feat_store_acc(float* Ss, int mw, int tx,
+                                               const v4f_t (&acc)[T::NTW][RT])
+{
+#pragma unroll
+    for (int i = 0; i < T::NTW; ++i)
+#pragma unroll
+        for (int r = 0; r < RT; ++r)
+            *reinterpret_cast<v4f_t*>(Ss + (16 * r + (tx & 15)) * T::SLD +
+                                      16 * (mw * T::NTW + i) + 4 * (tx >> 4)) = acc[i][r];
+}
+
+// LDS written by this wavefront becomes visible to its other lanes.
+__device__ __forceinline__ void wave_lds_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The actions of epilogue wavefront ew's envs -> act (bytes [EPW][kMaxAgents]):
+// read where the policy kernel sampled them, else Gumbel-max over the slot's
+// logits, four lanes per slot, lane b taking Philox block b (actions 8b .. 8b+7);
+// the slot's best is combined by two shuffles (larger z, the lower action on
+// equal z).  Envs past the end take action 0.
+// (given: this lane's byte of the former, loaded by the caller).
+template <class T>
+__device__ __forceinline__ void feat_actions(const FeatArgs& f, int64_t e0, int ew, int tx,
+                                             int given, uint8_t* act)
+{
+    const EnvArgs& ea = f.ea;
+    const SampleArgs& sa = f.sa;
+    const int slots = T::EPW * ea.n_agents;
+    auto put = [&](int i, int el, int64_t e, int a) {
+        const int seat = i - (el - ew * T::EPW) * ea.n_agents;
+        if (e < f.n) {
             if (sa.log)
-                sa.log[slot] = (uint8_t)a;
+                sa.log[e * ea.n_agents + seat] = (uint8_t)a;
             if (ea.tr.act)
-                ea.tr.act[traj_rec(ea.tr, sa.t, n, e) * ea.n_agents + seat] = (uint8_t)a;
+                ea.tr.act[traj_rec(ea.tr, sa.t, f.n, e) * ea.n_agents + seat] = (uint8_t)a;
         }
-        act_s[el * kMaxAgents + seat] = (uint8_t)a;
-    }
-    __syncthreads();
-    // the actions of this thread's envs, 8 bits per seat (bytes of seats
-    // >= n_agents are never read)
-    // (a wavefront's envs are the same for all its lanes: the action bytes, and
-    // with them the embedding rows' addresses, are kept in scalar registers)
-    uint64_t act_pk[EPT];
-#pragma unroll
-    for (int i = 0; i < EPT; ++i) {
-        const uint64_t pk =
-            *reinterpret_cast<const uint64_t*>(act_s + (ty * EPT + i) * kMaxAgents);
-        act_pk[i] = (uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)pk) |
-                    ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(pk >> 32)) << 32);
-    }
-
-    float acc[EPT][NJ];
-#pragma unroll
-    for (int i = 0; i < EPT; ++i)
-#pragma unroll
-        for (int j = 0; j < NJ; ++j)
-            acc[i][j] = 0.0f;
-
-    // trajectory observation of the step: bf16(s) of each env, written by the
-    // threads that stage the state chunks
-    uint16_t* obs_row = nullptr;
-    if (ea.tr.obs && s_owner && e_ld < n)
-        obs_row = (uint16_t*)ea.tr.obs + traj_rec(ea.tr, sa.t, n, e_ld) * D + cq_ld * 4;
-    for (int c0 = 0; c0 < D; c0 += kFeatKC) {
-        v4f* dst = reinterpret_cast<v4f*>(Ws);
-#pragma unroll
-        for (int q = 0; q < WQ; ++q)
-            dst[q * kFeatThreads + tid] = wreg[q];
-        if (e_ld >= n)
-            sreg = v4f{0.f, 0.f, 0.f, 0.f};
-        if (obs_row)
-            *reinterpret_cast<uint2*>(obs_row + c0) =
-                make_uint2(pack_bf16x2(sreg.x, sreg.y), pack_bf16x2(sreg.z, sreg.w));
-        if (s_owner) {
-            Ss[(cq_ld * 4 + 0) * SSTR + el_ld] = sreg.x;
-            Ss[(cq_ld * 4 + 1) * SSTR + el_ld] = sreg.y;
-            Ss[(cq_ld * 4 + 2) * SSTR + el_ld] = sreg.z;
-            Ss[(cq_ld * 4 + 3) * SSTR + el_ld] = sreg.w;
+        act[(el - ew * T::EPW) * kMaxAgents + seat] = (uint8_t)a;
+    };
+    if (sa.actions) {
+        if (tx < slots) {   // at most 4 envs x 8 seats
+            const int el = ew * T::EPW + tx / ea.n_agents;
+            put(tx, el, e0 + el, given);
         }
-        __syncthreads();
-        {
-            // next chunk (the last iteration re-reads its own chunk, unused)
-            const int cn = c0 + kFeatKC < D ? c0 + kFeatKC : c0;
-            const v4f* wn = wsrc + cn * (D / 4);
+    } else {
+        for (int i0 = 0; i0 < slots; i0 += 16) {
+            const int i = i0 + (tx >> 2), b = tx & 3;
+            const int el = ew * T::EPW + i / ea.n_agents;
+            const int64_t e = e0 + el;
+            const bool live = i < slots && e < f.n;
+            float zbest = -__builtin_inff();
+            int best = -1;
+            bool bad = false;
+            if (live && 8 * b < ea.A) {
+                const int seat = i - (el - ew * T::EPW) * ea.n_agents;
+                const float* l = sa.logits + (e * ea.n_agents + seat) * ea.A;
+                float lv[8];
 #pragma unroll
-            for (int q = 0; q < WQ; ++q)
-                wreg[q] = wn[q * kFeatThreads];
-            sreg = *reinterpret_cast<const v4f*>(ssrc + cn);
-        }
+                for (int j = 0; j < 8; ++j)
+                    lv[j] = l[8 * b + j < ea.A ? 8 * b + j : ea.A - 1];
+                const u64x4 blk = stream_block(sa.seed, (uint64_t)(sa.env_offset + e),
+                                               (uint64_t)sa.t, kPurposeAction, (uint32_t)seat,
+                                               (uint64_t)b);
 #pragma unroll
-        for (int c = 0; c < kFeatKC; ++c) {
-            float w[NJ];
-#pragma unroll
-            for (int g = 0; g < NG; ++g) {
-                FVec<GW> t;
-                t.load(&Ws[c * D + g * 64 * GW + GW * tx]);
-#pragma unroll
-                for (int j = 0; j < GW; ++j)
-                    w[g * GW + j] = t.v[j];
-            }
-            float sv[EPT];
-            if constexpr (EPT % 4 == 0) {
-                const v4f* sp = reinterpret_cast<const v4f*>(&Ss[c * SSTR + ty * EPT]);
-#pragma unroll
-                for (int q = 0; q < EPT / 4; ++q) {
-                    v4f t4 = sp[q];
-                    sv[4 * q + 0] = t4.x;
-                    sv[4 * q + 1] = t4.y;
-                    sv[4 * q + 2] = t4.z;
-                    sv[4 * q + 3] = t4.w;
+                for (int j = 0; j < 8; ++j) {
+                    const float z = lv[j] + gumbel01(uniform01(block_lane(blk, j)));
+                    bad |= __builtin_isnan(lv[j]);
+                    if (8 * b + j < ea.A && (best < 0 || z > zbest)) {
+                        zbest = z;
+                        best = 8 * b + j;
+                    }
                 }
-            } else {
-#pragma unroll
-                for (int i = 0; i < EPT; ++i)
-                    sv[i] = Ss[c * SSTR + ty * EPT + i];
             }
 #pragma unroll
-            for (int i = 0; i < EPT; ++i)
-#pragma unroll
-                for (int j = 0; j < NJ; ++j)
-                    acc[i][j] = __builtin_fmaf(w[j], sv[i], acc[i][j]);
+            for (int m = 1; m <= 2; m <<= 1) {
+                const float zo = __shfl_xor(zbest, m, 64);
+                const int bo = __shfl_xor(best, m, 64);
+                if (bo >= 0 && (best < 0 || zo > zbest || (zo == zbest && bo < best))) {
+                    zbest = zo;
+                    best = bo;
+                }
+                bad |= __shfl_xor((int)bad, m, 64) != 0;
+            }
+            if (b == 0 && i < slots) {
+                if (live && bad)
+                    atomicOr(sa.flags, kErrNaN);
+                put(i, el, e, live && !bad ? best : 0);
+            }
         }
-        __syncthreads();
     }
+    wave_lds_sync();
+}
 
-    // epilogue: embeddings in seat order (seat-outer so that each seat's loads
-    // for all of the thread's outputs are independent), tanh_ref, store s'
-    float* Sl = Ws;   // [kFeatEnvs][SLD]
-    float pre[EPT][NJ];
+// Epilogue of wavefront ew's envs (rows of Ss, all outputs of an env in one
+// wavefront): embeddings in seat order, tanh_ref, s' out and back into Ss.
+template <class T>
+__device__ __forceinline__ void feat_epilogue(const FeatArgs& f, int64_t e0, float* Ss,
+                                              const uint8_t* act, int ew, int tx)
+{
+    constexpr int EPW = T::EPW, GW = T::GW, NG = T::NG, D = 4 * T::Q4;
+    const EnvArgs& ea = f.ea;
+    // all embedding loads of an env are issued together.  The env is the same
+    // for all lanes: its action bytes, and with them the embedding rows'
+    // addresses, are kept in scalar registers.
 #pragma unroll
-    for (int i = 0; i < EPT; ++i)
+    for (int i = 0; i < EPW; ++i) {
+        const int el = ew * EPW + i;
+        const int64_t e = e0 + el;
+        const uint64_t pk = *reinterpret_cast<const uint64_t*>(act + i * kMaxAgents);
+        const uint64_t acts =
+            (uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)pk) |
+            ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(pk >> 32)) << 32);
+        FVec<GW> t[kMaxAgents][NG];
 #pragma unroll
-        for (int j = 0; j < NJ; ++j)
-            pre[i][j] = acc[i][j];
+        for (int q = 0; q < kMaxAgents; ++q)
+            if (q < ea.n_agents) {
+                const int a_q = (int)((acts >> (8 * q)) & 0xFFu);
+                const float* row = f.emb + (q * ea.A + a_q) * D + GW * tx;
 #pragma unroll
-    for (int q = 0; q < kMaxAgents; ++q) {
-        if (q < ea.n_agents) {
-            int off[EPT];
-#pragma unroll
-            for (int i = 0; i < EPT; ++i) {
-                const int a_q = (int)((act_pk[i] >> (8 * q)) & 0xFFu);
-                off[i] = (q * ea.A + a_q) * D + GW * tx;
+                for (int g = 0; g < NG; ++g)
+                    t[q][g].load(row + g * 64 * GW);
             }
+        FVec<GW> pre[NG];
 #pragma unroll
-            for (int i = 0; i < EPT; ++i)
+        for (int g = 0; g < NG; ++g)
+            pre[g].load(Ss + el * T::SLD + g * 64 * GW + GW * tx);
 #pragma unroll
-                for (int g = 0; g < NG; ++g) {
-                    FVec<GW> t;
-                    t.load(emb + off[i] + g * 64 * GW);
+        for (int q = 0; q < kMaxAgents; ++q)
+            if (q < ea.n_agents)
+#pragma unroll
+                for (int g = 0; g < NG; ++g)
 #pragma unroll
                     for (int j = 0; j < GW; ++j)
-                        pre[i][g * GW + j] = pre[i][g * GW + j] + t.v[j];
-                }
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < EPT; ++i) {
-        const int el = ty * EPT + i;
-        const int64_t e = e0 + el;
+                        pre[g].v[j] = pre[g].v[j] + t[q][g].v[j];
 #pragma unroll
         for (int g = 0; g < NG; ++g) {
             const int k0 = g * 64 * GW + GW * tx;
-            FVec<GW> t;
 #pragma unroll
             for (int j = 0; j < GW; ++j)
-                t.v[j] = tanh_ref(pre[i][g * GW + j]);
-            if (e < n) {
-                t.store(s_out + e * D + k0);
+                pre[g].v[j] = tanh_ref(pre[g].v[j]);
+            if (e < f.n) {
+                pre[g].store(f.s_out + e * D + k0);
                 if (ea.obs)
-                    store_bf16<GW>(ea.obs + e * D + k0, t);
+                    store_bf16<GW>(ea.obs + e * D + k0, pre[g]);
             }
-            t.store(Sl + el * SLD + k0);
+            pre[g].store(Ss + el * T::SLD + k0);
         }
     }
+}
+
+// One tile per workgroup.  Two 32-env workgroups share a CU; a batch of at most
+// one 16-env tile per CU takes 16 wavefronts per tile, being bound by one tile's
+// latency.
+template <int D, int RT, int WAVES, int DEPTH>
+__global__ __launch_bounds__(64 * WAVES, 4) void step_feature_kernel(FeatArgs f)
+{
+    using T = FeatTile<D, RT, WAVES>;
+    constexpr int THREADS = 64 * WAVES;
+    __shared__ __attribute__((aligned(16))) float Ss[T::E * T::SLD];
+    // the reward weights u, staged once: the chain reads both operands from LDS
+    __shared__ __attribute__((aligned(16))) float Us[D];
+    __shared__ __attribute__((aligned(8))) uint8_t act_s[T::E * kMaxAgents];
+    const int tid = threadIdx.x, tx = tid & 63;
+    const int ty = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t e0 = (int64_t)blockIdx.x * T::E;
+    const EnvArgs& ea = f.ea;
+    v4f_t sreg[T::SQ], a[DEPTH][T::NTW], acc[T::NTW][RT];
+    feat_load_state<T>(f, e0, tid, THREADS, sreg);
+    // u and the given actions before W: loads complete in order
+    constexpr int UQ = (D + THREADS - 1) / THREADS;
+    float ureg[UQ];
+#pragma unroll
+    for (int k = 0; k < UQ; ++k)
+        ureg[k] = k * THREADS + tid < D ? f.u[k * THREADS + tid] : 0.f;
+    const int64_t slot0 = (e0 + ty * T::EPW) * ea.n_agents + tx;
+    int given = 0;
+    if (f.sa.actions && tx < T::EPW * ea.n_agents && slot0 < f.n * ea.n_agents)
+        given = f.sa.actions[slot0];
+    const WSrc W = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(f.WP), (short)0,
+                                                     D * D * 4, 0x00020000);
+    auto fill = [&] {
+#pragma unroll
+        for (int s = 0; s < DEPTH; ++s)
+#pragma unroll
+            for (int i = 0; i < T::NTW; ++i)
+                a[s][i] = load_w4(W, (ty * T::NTW + i) * T::KG + s, tx * 16);
+    };
+    // the first W operands at once where registers allow, else after the actions
+    constexpr bool kEarly = DEPTH * T::NTW + T::SQ <= 12;
+    if constexpr (kEarly)
+        fill();
+#pragma unroll
+    for (int k = 0; k < UQ; ++k)
+        if (k * THREADS + tid < D)
+            Us[k * THREADS + tid] = ureg[k];
+    uint8_t* act = act_s + ty * T::EPW * kMaxAgents;
+    feat_actions<T>(f, e0, ty, tx, given, act);
+    if constexpr (!kEarly)
+        fill();
+    feat_stage_state<T>(Ss, tid, THREADS, sreg);
+    feat_record_obs<T>(f, e0, tid, THREADS, sreg);
+    __syncthreads();
+    feat_mfma<T, RT, DEPTH>(W, Ss, ty, tx, a, acc);
+    __syncthreads();   // every wavefront is done with the state rows
+    feat_store_acc<T, RT>(Ss, ty, tx, acc);
+    __syncthreads();
+    feat_epilogue<T>(f, e0, Ss, act, ty, tx);
     // reward chain of the workgroup's envs (one lane each); the seats' running
     // returns are fetched before the chain so their latency overlaps it, and
     // the chain is unrolled so that its LDS loads run ahead of the dependent
     // FMAs
     const int64_t er = e0 + tid;
-    const bool rlane = tid < kFeatEnvs && er < n;
+    const bool rlane = tid < T::E && er < f.n;
     float rv[kMaxAgents];
 #pragma unroll
     for (int q = 0; q < kMaxAgents; ++q)
         if (rlane && q < ea.n_agents)
-            rv[q] = ret[(int64_t)q * n + er];
+            rv[q] = f.ret[(int64_t)q * f.n + er];
     __syncthreads();
     if (rlane) {
         float r = 0.0f;
-        const float* row = Sl + tid * SLD;
-        const float* u = Us;
-#pragma unroll
+        const float* row = Ss + tid * T::SLD;
+#pragma unroll 64
         for (int k = 0; k < D; ++k)
-            r = __builtin_fmaf(u[k], row[k], r);
+            r = __builtin_fmaf(Us[k], row[k], r);
 #pragma unroll
         for (int q = 0; q < kMaxAgents; ++q)
             if (q < ea.n_agents)
-                ret[(int64_t)q * n + er] = rv[q] + (((ea.team_row >> q) & 1u) ? r : -r);
+                f.ret[(int64_t)q * f.n + er] = rv[q] + (((ea.team_row >> q) & 1u) ? r : -r);
         if (ea.tr.rew) {
-            const int64_t rec = traj_rec(ea.tr, sa.t, n, er);
+            const int64_t rec = traj_rec(ea.tr, f.sa.t, f.n, er);
             ea.tr.rew[rec] = r;
-            ea.tr.flags[rec] = sa.t == ea.tr.horizon - 1 ? 2 : 0;
+            ea.tr.flags[rec] = f.sa.t == ea.tr.horizon - 1 ? 2 : 0;
         }
     }
+}
+
+template <int D, int RT, int WAVES, int DEPTH>
+static void launch_feature(const FeatArgs& f, hipStream_t s)
+{
+    const int blocks = (int)((f.n + 16 * RT - 1) / (16 * RT));
+    step_feature_kernel<D, RT, WAVES, DEPTH><<<blocks, 64 * WAVES, 0, s>>>(f);
 }
 
 hipError_t launch_env_step(const EnvArgs& e, const SampleArgs& sa, int64_t n_envs,
@@ -603,33 +760,31 @@ hipError_t launch_env_step(const EnvArgs& e, const SampleArgs& sa, int64_t n_env
             e.grid, n_envs, sa, e.tr, (uint8_t*)state_out, done, ret, frames);
         break;
     case MALIB_ENV_FEATURE: {
-        const float* si = (const float*)state_in;
-        float* so = (float*)state_out;
         if (e.A > kMaxActions)
             return hipErrorInvalidValue;
-        // 8 envs per thread for d = 512 (64-env workgroups), 4 below (32 envs);
-        // at d = 256 a batch too small for one such workgroup per CU takes 2 or
-        // 1 env per thread instead (16- or 8-env workgroups): the step of a
-        // small batch is latency-bound, and more workgroups shorten it (4v4
-        // game: 4096 envs 28.9 -> 25.0 us with 2, 2048 envs 27.3 -> 20.9 us and
-        // 257 envs 26.3 -> 19.0 us with 1; the sums are the same per output)
+        const FeatArgs f{e.WP, e.emb, e.u, e, sa, n_envs, (const float*)state_in,
+                         (float*)state_out, ret};
+        // 16-env tiles up to one per CU, 32-env tiles (half the W traffic per
+        // env) beyond that: at d = 256, 4096 envs take 13 us with 16-env tiles,
+        // 6000 envs 19.2 us with 32-env and 22.6 us with 16-env tiles
         const int64_t cus = e.n_cus > 0 ? e.n_cus : 256;
-        const int fb8 = (int)((n_envs + 8 * kFeatWaves - 1) / (8 * kFeatWaves));
-        const int fb4 = (int)((n_envs + 4 * kFeatWaves - 1) / (4 * kFeatWaves));
-        const int fb2 = (int)((n_envs + 2 * kFeatWaves - 1) / (2 * kFeatWaves));
-        const int fb1 = (int)((n_envs + kFeatWaves - 1) / kFeatWaves);
-        if (e.d == 64)
-            step_feature_kernel<64, 4><<<fb4, kFeatThreads, 0, s>>>(e.WT, e.emb, e.u, e, sa, n_envs, si, so, ret);
+        const bool small = n_envs <= 16 * cus;
+        if (e.d == 64 && small)
+            launch_feature<64, 1, 4, 4>(f, s);
+        else if (e.d == 64)
+            launch_feature<64, 2, 4, 4>(f, s);
+        else if (e.d == 128 && small)
+            launch_feature<128, 1, 8, 8>(f, s);
         else if (e.d == 128)
-            step_feature_kernel<128, 4><<<fb4, kFeatThreads, 0, s>>>(e.WT, e.emb, e.u, e, sa, n_envs, si, so, ret);
-        else if (e.d == 256 && n_envs >= 4 * kFeatWaves * cus)
-            step_feature_kernel<256, 4><<<fb4, kFeatThreads, 0, s>>>(e.WT, e.emb, e.u, e, sa, n_envs, si, so, ret);
-        else if (e.d == 256 && n_envs >= 2 * kFeatWaves * cus)
-            step_feature_kernel<256, 2><<<fb2, kFeatThreads, 0, s>>>(e.WT, e.emb, e.u, e, sa, n_envs, si, so, ret);
+            launch_feature<128, 2, 8, 4>(f, s);
+        else if (e.d == 256 && small)
+            launch_feature<256, 1, 16, 8>(f, s);
         else if (e.d == 256)
-            step_feature_kernel<256, 1><<<fb1, kFeatThreads, 0, s>>>(e.WT, e.emb, e.u, e, sa, n_envs, si, so, ret);
+            launch_feature<256, 2, 8, 2>(f, s);
+        else if (e.d == 512 && small)
+            launch_feature<512, 1, 16, 4>(f, s);
         else if (e.d == 512)
-            step_feature_kernel<512, 8><<<fb8, kFeatThreads, 0, s>>>(e.WT, e.emb, e.u, e, sa, n_envs, si, so, ret);
+            launch_feature<512, 2, 8, 2>(f, s);
         else
             return hipErrorInvalidValue;
         break;

@@ -1,0 +1,57 @@
+"""The feature dynamics' step kernel at the sizes where its tiling can go
+wrong: one env, one less and one more than a 16- or 32-env tile, the last
+batch of 16-env tiles (16 per CU) and the first of 32-env tiles, for every
+state width; given and kernel-sampled actions, 2 to 8 seats.  States, returns
+and rewards are compared bit for bit with the oracle's sequential fused chain
+(gpu_helpers.check_parity), also where products, sums and states are subnormal."""
+import numpy as np
+import pytest
+
+import workloads as W
+from gpu_helpers import check_parity, run_gpu, say
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+def _edges(n, rng):
+    """Envs around every tile boundary near both ends, and a few others."""
+    at = {0, 15, 16, 31, 32, n // 2, n - 33, n - 32, n - 17, n - 16, n - 1}
+    at |= set(rng.integers(0, n, size=6).tolist())
+    return np.array(sorted(e for e in at if 0 <= e < n))
+
+
+@pytest.mark.parametrize("sampled", [False, True])
+@pytest.mark.parametrize("d", [64, 128, 256, 512])
+def test_step_tile_edges(d, sampled):
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    for k, n in enumerate([1, 15, 16, 17, 33, 16 * cus, 16 * cus + 1, 32 * cus + 31]):
+        seats = [2, 8, 3, 5][k % 4]
+        # fp32 policies leave the sampling to the step kernel
+        wl = W.team_variant(seats, d=d, P=3, n_envs=n, horizon=2)
+        if sampled:
+            wl = W.with_policies(wl, W.MLP_F32, [d, 32, 32, 18])
+        say(f"[step] d={d} n={n} seats={seats} sampled={sampled}")
+        sel = np.arange(n) if n < 64 else _edges(n, np.random.default_rng(n))
+        check_parity(wl, run_gpu(wl, snaps=[0, 1]), sel)
+
+
+@pytest.mark.parametrize("n", [33, 4200])
+@pytest.mark.parametrize("d", [64, 256])
+def test_step_subnormal_sums(d, n):
+    """Dynamics scaled so that the chains' products and sums, the embeddings
+    and from the second step on the states are subnormal."""
+    wl = W.team_variant(2, d=d, P=3, n_envs=n, horizon=3)
+    wl.W = (wl.W * np.float32(2.0 ** -128)).astype(np.float32)
+    wl.emb = (wl.emb * np.float32(2.0 ** -130)).astype(np.float32)
+    wl.u = (wl.u * np.float32(2.0 ** 20)).astype(np.float32)
+    g = run_gpu(wl, snaps=[0, 1, 2])
+    s1 = np.abs(g["states"][1])
+    assert ((s1 > 0) & (s1 < np.finfo(np.float32).tiny)).mean() > 0.9
+    check_parity(wl, g, np.arange(n) if n < 64 else _edges(n, np.random.default_rng(1)))
