@@ -239,7 +239,7 @@ static size_t weight_bytes(const Pop& p, int l)
 {
     const int fi = p.dims[l], fo = p.dims[l + 1];
     if (p.generic)
-        return (p.kind == MALIB_POLICY_MLP_F32 ? 4 : 2) * (size_t)fo * fi;
+        return (p.kind == MALIB_POLICY_MLP_F32 ? 4 : 2) * (size_t)generic_weight_elems(fo, fi);
     if (p.kind == MALIB_POLICY_MLP_F32)
         return sizeof(float) * (size_t)fo * fi;
     const int ip = l == 0 ? p.in_pad : round_up(fi, 16);
@@ -248,18 +248,13 @@ static size_t weight_bytes(const Pop& p, int l)
 }
 
 // k policies' fp32 weights of layer l ([k][out][in], device) into the
-// handle's layout at dst: the generic kernel's [k][out][in] (fp32, or bf16
-// bits), or the specialized kernels' packed MFMA operand layouts.
+// handle's layout at dst: the kernels' packed MFMA operand layouts.
 static hipError_t store_weights(const Pop& p, int l, const float* src, int k, void* dst,
                                 hipStream_t s)
 {
     const int fi = p.dims[l], fo = p.dims[l + 1];
-    if (p.generic) {
-        const int64_t n = (int64_t)k * fo * fi;
-        if (p.kind == MALIB_POLICY_MLP_F32)
-            return hipMemcpyAsync(dst, src, sizeof(float) * n, hipMemcpyDeviceToDevice, s);
-        return launch_round_bf16(src, n, (uint16_t*)dst, s);
-    }
+    if (p.generic)
+        return launch_pack_generic(src, k, fo, fi, p.kind == MALIB_POLICY_MLP_BF16, dst, s);
     if (p.kind == MALIB_POLICY_MLP_F32)
         return launch_pack_f32(src, k, l, p.hid, p.A, (float*)dst, s);
     const int ip = l == 0 ? p.in_pad : round_up(fi, 16);
@@ -594,7 +589,7 @@ struct RolloutPlan {
     int64_t ns = 0;               // agent slots
     bool mlp = false, persist = false, bf16_obs = false;
     bool kernel_sample = false;   // the 64-row policy kernel samples the actions
-    bool striped = false;         // tile table in XCD segments (the 64-row kernel)
+    bool striped = false;         // tile table in XCD segments (64-row and generic kernels)
     int tile_rows = 0, max_tiles = 0, n_chunks = 0;
     int64_t state_bytes = 0;      // one state buffer (FEATURE has two)
 };
@@ -715,11 +710,11 @@ static malib_status plan_rollout(malib_pop_t pop, const malib_env_desc* env, int
     plan.mlp = pop->kind != MALIB_POLICY_TABULAR;
     plan.persist = pop->kind == MALIB_POLICY_MLP_BF16 && !pop->generic &&
                    use_persist_kernel(env->kind, pop->in_pad, ns, pop->P);
-    plan.tile_rows = pop->generic ? kGenericTileRows
+    plan.tile_rows = pop->generic ? generic_tile_rows(pop->dims, ns, pop->n_cus)
                      : pop->kind == MALIB_POLICY_MLP_BF16
                          ? (plan.persist ? kPersistRows : kBf16TileRows)
                          : kF32TileRows;
-    plan.striped = pop->kind == MALIB_POLICY_MLP_BF16 && !pop->generic && !plan.persist;
+    plan.striped = pop->generic || (pop->kind == MALIB_POLICY_MLP_BF16 && !plan.persist);
     plan.max_tiles = plan.striped ? striped_entries(ns, pop->P, plan.tile_rows)
                                   : max_tiles_for(ns, pop->P, plan.tile_rows);
     plan.n_chunks = (int)((ns + kBucketChunk - 1) / kBucketChunk);
@@ -892,7 +887,8 @@ static malib_status launch_rollout(malib_pop_t pop, const malib_env_desc* env, i
                                    logits, s));
         else if (pop->generic)
             HIP_TRY(launch_mlp_generic(*pop, env->kind, n_agents, env->grid, b.perm, b.perm_env,
-                                       b.tile_info, plan.max_tiles, ns, cur, logits, s));
+                                       b.tile_info, plan.max_tiles, plan.tile_rows, ns, cur, logits,
+                                       s));
         else if (pop->kind == MALIB_POLICY_MLP_F32)
             HIP_TRY(launch_mlp_f32(*pop, b.perm, b.tile_info, ns, n_agents, cur, logits, s));
         else if (persist)

@@ -44,8 +44,8 @@ struct Pop {
     int A = 0;
     int in_dim = 0, hid = 0;
     int in_pad = 0;               // bf16: input padded to a multiple of 16
-    // generic MLP (shapes the specialized kernels do not take): weights kept
-    // as [P][out][in] (fp32, or bf16 bits), dims = {in, h1, h2, A}
+    // generic MLP (shapes the specialized kernels do not take): weights packed
+    // as fp32 MFMA operands (fp32, or bf16 bits), dims = {in, h1, h2, A}
     bool generic = false;
     int dims[4] = {0, 0, 0, 0};
     int device = 0;
@@ -259,15 +259,31 @@ hipError_t launch_mlp_bf16(const Pop& pop, int env_kind, int n_agents, int grid,
                            int tile_rows, const int32_t* perm, const int32_t* perm_env,
                            const int4* tile_info, int64_t n_slots, const void* state,
                            float* logits, const KernelSample* ks, hipStream_t s);
-// Generic MLP forward (k_policy.hip): tiles of kGenericTileRows rows, widths
-// up to kGenericMaxWidth; logits for the env step to sample.
-constexpr int kGenericTileRows = 8;
+// Generic MLP forward (k_policy.hip): widths up to kGenericMaxWidth, logits for
+// the env step to sample; striped tile table of generic_tile_rows() rows.
 constexpr int kGenericMaxWidth = 1024;
+// Rows of a tile: 16, which fill the chip sooner, or 32, which halve the weight
+// traffic per row, from 48 rows per CU on (fp32 256-512-400-18: 8000 rows 65 us
+// with 16-row and 106 us with 32-row tiles, 32000 rows 224 and 205 us;
+// 128-256-256-18: 2400 rows 18 and 25 us, 16000 rows 44 and 42 us); always 16
+// above width 512, where 32 rows would leave one workgroup per CU.
+inline int generic_tile_rows(const int (&dims)[4], int64_t n_slots, int n_cus)
+{
+    const int widest = std::max(dims[0], std::max(dims[1], dims[2]));
+    return widest <= 512 && n_slots >= 48 * (int64_t)n_cus ? 32 : 16;
+}
+// Elements of one policy's packed weights of a layer (units padded to 16,
+// inputs to 32).
+inline int64_t generic_weight_elems(int out, int in)
+{
+    return (int64_t)((out + 15) / 16 * 16) * ((in + 31) / 32 * 32);
+}
 hipError_t launch_mlp_generic(const Pop& pop, int env_kind, int n_agents, int grid,
                               const int32_t* perm, const int32_t* perm_env,
-                              const int4* tile_info, int max_tiles, int64_t n_slots,
-                              const void* state, float* logits, hipStream_t s);
-hipError_t launch_round_bf16(const float* w, int64_t n, uint16_t* out, hipStream_t s);
+                              const int4* tile_info, int max_tiles, int tile_rows,
+                              int64_t n_slots, const void* state, float* logits, hipStream_t s);
+hipError_t launch_pack_generic(const float* w, int P, int out, int in, bool bf16, void* dst,
+                               hipStream_t s);
 // Feature observations of d = 512 with >= 256 slots per policy on average:
 // persistent kernel over 128-row tiles (one eight-wave workgroup per CU, output
 // layer fed from the layer-2 accumulators).  For narrower observations the

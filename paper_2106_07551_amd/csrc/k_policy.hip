@@ -1036,23 +1036,36 @@ __global__ __launch_bounds__(bf16_tile_threads(HID), bf16_tile_waves_per_simd(HI
 // ------------------------------------------------------------ generic MLP
 
 // Any MLP the specialized kernels do not cover (input and hidden widths up to
-// 1024 each, the two hidden widths free, fp32 policies on every environment):
-// one workgroup per tile of kGenericTileRows rows of one policy; the rows'
-// activations in LDS (fp32 values; bf16-rounded for bf16 policies), each
-// thread forms output units tid, tid + 256, ... for every row with an fp32
-// fused multiply-add chain over the inputs, then adds the bias, applies the
-// hidden ReLU (IEEE maximum with +0: a NaN stays NaN) and, for bf16
-// policies, rounds to bf16 (products of bf16 values are exact in fp32).
-// Weights are kept as given, [P][out][in] (fp32, or bf16 bits rounded to
-// nearest even at creation).  The logits go to the env step, which samples.
+// 1024 each, the two hidden widths free, fp32 policies on every environment).
+// A unit is a fused multiply-add chain over the inputs in ascending order from
+// 0, then the bias, the hidden ReLU (IEEE maximum with +0: a NaN stays NaN) and,
+// for bf16 policies, rounding to bf16 (products of bf16 values are exact in
+// fp32).  The logits go to the env step, which samples.
+//
+// The chains run on v_mfma_f32_16x16x4_f32, which adds its products in
+// ascending k with one rounding each (see step_feature_kernel): A = weights (16
+// units x 4 inputs), B = activations (4 inputs x 16 rows) from LDS, where the 16
+// inputs of a group sit in operand order (input 4 j + m at 4 m + j).  Weights are
+// packed once at creation in operand order, units padded to 16 and inputs to 32
+// with zeros (which leave a chain as it is), fp32 or bf16 bits (widened in
+// registers), and streamed from the L2 through buffer resources.  One workgroup
+// of 8 wavefronts per tile of 16 RT rows of one policy; wavefront w takes the
+// units' tiles w, w + 8, ...; all of a layer's accumulators stay in registers
+// until every wavefront has read its inputs, then replace them in LDS.
+//
+// Bound: fp32 MFMA (157 TFLOP/s; the same SIMD cycles as the VALU), and at small
+// batches one tile's latency.  bf16 256-1024-1024-18, 9600 rows of 12 policies in
+// equal buckets: 210 us (122 TFLOP/s); fp32 128-256-256-18, 16000 rows: 39 us.
+// (One thread per unit with 8-row tiles took 3970 and 765 us.)
 
-constexpr int kGenericThreads = 256;
+constexpr int kGenericThreads = 512;
 
 struct MlpGenericArgs {
     const void* w[3];
     const float* b[3];
     int dims[4];
-    int bf16;
+    int kg2[3];             // pairs of 16-input groups per layer
+    int sld;                // row stride of the activations in LDS
     const int32_t* perm;
     const int32_t* perm_env;
     const int4* tile_info;
@@ -1064,12 +1077,10 @@ struct MlpGenericArgs {
     float* logits;
 };
 
-// Observation element k of seat `seat` of env `env` (the encodings of the
-// other policy kernels, element by element).
+// Observation element k (0 or 1) of seat `seat` of env `env` in pursuit and the
+// iterated game (the encodings of the other policy kernels).
 __device__ __forceinline__ float generic_obs(const MlpGenericArgs& a, int env, int seat, int k)
 {
-    if (a.env_kind == MALIB_ENV_FEATURE)
-        return ((const float*)a.state)[(int64_t)env * a.dims[0] + k];
     if (a.env_kind == MALIB_ENV_PURSUIT) {
         const uint8_t* pos = (const uint8_t*)a.state;
         const int G = a.grid, pc = pos[env], ec = pos[a.n_envs + env];
@@ -1097,24 +1108,131 @@ __device__ __forceinline__ float bf16_value(float x)
     return __uint_as_float((uint32_t)bf16_bits(x) << 16);
 }
 
-__device__ __forceinline__ float generic_weight(const MlpGenericArgs& a, int l, int64_t i)
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+
+// Weights of NI of a layer's unit tiles for one group of 16 inputs, as loaded.
+template <bool BF16, int NI>
+struct GenericW {
+    uint4 f[BF16 ? 1 : NI];
+    uint2 h[BF16 ? NI : 1];
+};
+
+template <bool BF16, int NI>
+__device__ __forceinline__ void generic_load(GenericW<BF16, NI>& w, __amdgpu_buffer_rsrc_t src,
+                                             int nt0, int kgs, int g, int lane)
 {
-    if (a.bf16)
-        return __uint_as_float((uint32_t)((const uint16_t*)a.w[l])[i] << 16);
-    return ((const float*)a.w[l])[i];
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+        const int blk = (nt0 + 8 * i) * kgs + g;   // past the end: zeros
+        if constexpr (BF16) {
+            const auto v = __builtin_amdgcn_raw_buffer_load_b64(src, lane * 8, blk * 512, 0);
+            w.h[i] = make_uint2(v[0], v[1]);
+        } else {
+            const auto v = __builtin_amdgcn_raw_buffer_load_b128(src, lane * 16, blk * 1024, 0);
+            w.f[i] = make_uint4(v[0], v[1], v[2], v[3]);
+        }
+    }
 }
 
-__global__ __launch_bounds__(kGenericThreads) void mlp_generic_kernel(MlpGenericArgs a)
+template <bool BF16, int NI>
+__device__ __forceinline__ f32x4_t generic_operand(const GenericW<BF16, NI>& w, int i)
 {
-    constexpr int R = kGenericTileRows, W = kGenericMaxWidth;
-    __shared__ float xa[R * W];
-    __shared__ float xb[R * W];
+    if constexpr (BF16)
+        return f32x4_t{__uint_as_float(w.h[i].x << 16), __uint_as_float(w.h[i].x & 0xFFFF0000u),
+                       __uint_as_float(w.h[i].y << 16), __uint_as_float(w.h[i].y & 0xFFFF0000u)};
+    else
+        return __builtin_bit_cast(f32x4_t, w.f[i]);
+}
+
+// acc[i][r]: units of tile nt0 + 8 i of row tile r (lane: row lane % 16, units
+// 4 (lane / 16) ..) = the chains over kgs (even) groups of 16 inputs.
+template <bool BF16, int NI, int RT>
+__device__ __forceinline__ void generic_chains(__amdgpu_buffer_rsrc_t src, int kgs, int nt0,
+                                               const float* bp, int sld, int lane,
+                                               f32x4_t (&acc)[NI][RT])
+{
+    // two groups of weights in flight (one where eight fp32 tiles fill the registers)
+    constexpr int DEPTH = !BF16 && NI > 6 ? 1 : 2;
+    GenericW<BF16, NI> w[DEPTH];
+#pragma unroll
+    for (int s = 0; s < DEPTH; ++s)
+        generic_load<BF16, NI>(w[s], src, nt0, kgs, s, lane);
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int r = 0; r < RT; ++r)
+            acc[i][r] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int g0 = 0; g0 < kgs; g0 += 2) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            f32x4_t b[RT];
+#pragma unroll
+            for (int r = 0; r < RT; ++r)
+                b[r] = *reinterpret_cast<const f32x4_t*>(bp + 16 * r * sld + 16 * (g0 + h));
+            f32x4_t a[NI];
+#pragma unroll
+            for (int i = 0; i < NI; ++i)
+                a[i] = generic_operand<BF16, NI>(w[h % DEPTH], i);
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int i = 0; i < NI; ++i)
+#pragma unroll
+                    for (int r = 0; r < RT; ++r)
+                        acc[i][r] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][j], b[r][j],
+                                                                         acc[i][r], 0, 0, 0);
+            if (g0 + h + DEPTH < kgs)
+                generic_load<BF16, NI>(w[h % DEPTH], src, nt0, kgs, g0 + h + DEPTH, lane);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+}
+
+// One hidden layer of the wavefront's NI tiles: chains, then (every wavefront
+// past its reads) bias, ReLU, rounding and the activations back into xs.
+template <bool BF16, int NI, int RT>
+__device__ __forceinline__ void generic_hidden(__amdgpu_buffer_rsrc_t src, int kgs, int nt0,
+                                               int out, const float* __restrict__ bias,
+                                               float* xs, int sld, int lane)
+{
+    f32x4_t acc[NI][RT];
+    generic_chains<BF16, NI, RT>(src, kgs, nt0, xs + (lane & 15) * sld + 4 * (lane >> 4), sld,
+                                 lane, acc);
+    __syncthreads();
+    const int q = lane >> 4;
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+        const int u0 = 16 * (nt0 + 8 * i);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            // unit u0 + 4 q + e is input 4 j + m of its group with j = q, m = e
+            const int o = u0 + 4 * q + e;
+            const float b = o < out ? bias[o] : 0.f;
+#pragma unroll
+            for (int r = 0; r < RT; ++r) {
+                float v = relu_f32(acc[i][r][e] + b);
+                if (BF16)
+                    v = bf16_value(v);
+                xs[(16 * r + (lane & 15)) * sld + u0 + 4 * e + q] = o < out ? v : 0.f;
+            }
+        }
+    }
+}
+
+// NTW: unit tiles per wavefront at most (widths up to 128 NTW), RT: row tiles.
+template <bool BF16, int NTW, int RT>
+__global__ __launch_bounds__(kGenericThreads, 4) void mlp_generic_kernel(MlpGenericArgs a)
+{
+    constexpr int R = 16 * RT, LDS_W = 128 * NTW + 4;
+    __shared__ __attribute__((aligned(16))) float xs[R * LDS_W];
     __shared__ int row_slot[R], row_env[R];
-    const int t = blockIdx.x, tid = threadIdx.x;
-    if (t >= a.max_tiles)
-        return;
-    const int4 ti = a.tile_info[t];
-    const int p = ti.x;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // striped tile table: one segment per XCD, so that a policy's tiles share an L2
+    const int per = a.max_tiles / 8;
+    const int4 ti = a.tile_info[(blockIdx.x & 7) * per + (blockIdx.x >> 3)];
+    const int p = __builtin_amdgcn_readfirstlane(ti.x);
     if (p < 0)
         return;
     if (tid < R) {
@@ -1122,58 +1240,98 @@ __global__ __launch_bounds__(kGenericThreads) void mlp_generic_kernel(MlpGeneric
         row_env[tid] = tid < ti.z ? a.perm_env[ti.y + tid] : -1;
     }
     __syncthreads();
-    const int in0 = a.dims[0];
-    for (int i = tid; i < R * in0; i += kGenericThreads) {
-        const int r = i / in0, k = i - r * in0;
-        const int env = row_env[r];
-        float v = 0.0f;
-        if (env >= 0)
-            v = generic_obs(a, env, row_slot[r] - env * a.n_agents, k);
-        xa[r * W + k] = a.bf16 ? bf16_value(v) : v;
+    const int sld = a.sld;
+    // observations (rounded for bf16 policies) in operand order
+    if (a.env_kind == MALIB_ENV_FEATURE) {
+        // the state's width, a multiple of 32: 16 bytes per thread
+        const int q4 = a.dims[0] / 4;
+        for (int i = tid; i < R * q4; i += kGenericThreads) {
+            const int r = i / q4, c4 = i - r * q4, env = row_env[r];
+            f32x4_t v = {0.f, 0.f, 0.f, 0.f};
+            if (env >= 0)
+                v = *reinterpret_cast<const f32x4_t*>((const float*)a.state +
+                                                      (int64_t)env * a.dims[0] + 4 * c4);
+            float* dst = xs + r * sld + (c4 >> 2) * 16 + (c4 & 3);
+#pragma unroll
+            for (int m = 0; m < 4; ++m)
+                dst[4 * m] = BF16 ? bf16_value(v[m]) : v[m];
+        }
+    } else {
+        // padded to whole pairs of groups
+        const int in0 = a.dims[0], pad = 32 * a.kg2[0];
+        for (int i = tid; i < R * pad; i += kGenericThreads) {
+            const int r = i / pad, k = i - r * pad;
+            const int env = row_env[r];
+            float v = 0.0f;
+            if (env >= 0 && k < in0)
+                v = generic_obs(a, env, row_slot[r] - env * a.n_agents, k);
+            xs[r * sld + (k & ~15) + 4 * (k & 3) + ((k >> 2) & 3)] = v;   // 0 or 1
+        }
     }
     __syncthreads();
-    float* x = xa;
-    float* y = xb;
-    for (int l = 0; l < 3; ++l) {
-        const int in = a.dims[l], out = a.dims[l + 1];
-        const int64_t wbase = (int64_t)p * out * in;
-        for (int o = tid; o < out; o += kGenericThreads) {
-            float acc[R];
-#pragma unroll
-            for (int r = 0; r < R; ++r)
-                acc[r] = 0.0f;
-            const int64_t wrow = wbase + (int64_t)o * in;
-            for (int k = 0; k < in; ++k) {
-                const float w = generic_weight(a, l, wrow + k);
-#pragma unroll
-                for (int r = 0; r < R; ++r)
-                    acc[r] = __builtin_fmaf(w, x[r * W + k], acc[r]);
-            }
-            const float b = a.b[l][(int64_t)p * out + o];
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                float v = acc[r] + b;
-                if (l < 2) {
-                    v = relu_f32(v);
-                    y[r * W + o] = a.bf16 ? bf16_value(v) : v;
-                } else if (r < ti.z) {
-                    a.logits[(int64_t)row_slot[r] * a.A + o] = v;
-                }
-            }
+#pragma unroll 1
+    for (int l = 0; l < 2; ++l) {
+        const int out = a.dims[l + 1], kgs = 2 * a.kg2[l];
+        const int nts = (out + 15) / 16;
+        const int64_t bytes = (int64_t)nts * kgs * (BF16 ? 512 : 1024);
+        const auto src = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<char*>((const char*)a.w[l] + p * bytes), (short)0, (int)bytes, 0x00020000);
+        const float* bias = a.b[l] + (int64_t)p * out;
+        // tiles of this wavefront: every wavefront passes the barrier inside
+        const int ni = wave < nts ? (nts - wave + 7) / 8 : 0;
+        switch (ni) {
+#define MALIB_GENERIC_CASE(N)                                                                   \
+    case N:                                                                                     \
+        if constexpr (N <= NTW)                                                                 \
+            generic_hidden<BF16, N, RT>(src, kgs, wave, out, bias, xs, sld, lane);              \
+        break;
+            MALIB_GENERIC_CASE(1)
+            MALIB_GENERIC_CASE(2)
+            MALIB_GENERIC_CASE(3)
+            MALIB_GENERIC_CASE(4)
+            MALIB_GENERIC_CASE(5)
+            MALIB_GENERIC_CASE(6)
+            MALIB_GENERIC_CASE(7)
+            MALIB_GENERIC_CASE(8)
+#undef MALIB_GENERIC_CASE
+        default:
+            __syncthreads();
         }
+        // an odd number of unit tiles: the next layer's last group of inputs
+        if ((nts & 1) && tid < R * 16)
+            xs[(tid >> 4) * sld + 16 * nts + (tid & 15)] = 0.f;
         __syncthreads();
-        float* tmp = x;
-        x = y;
-        y = tmp;
+    }
+    // output layer (at most 32 logits): one (unit tile, row tile) per wavefront
+    const int A = a.dims[3], kgs = 2 * a.kg2[2], nts = (A + 15) / 16;
+    if (wave < nts * RT) {
+        const int nt = wave % nts, rt = wave / nts;
+        const int64_t bytes = (int64_t)nts * kgs * (BF16 ? 512 : 1024);
+        const auto src = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<char*>((const char*)a.w[2] + p * bytes), (short)0, (int)bytes, 0x00020000);
+        f32x4_t acc[1][1];
+        generic_chains<BF16, 1, 1>(src, kgs, nt,
+                                   xs + (16 * rt + (lane & 15)) * sld + 4 * (lane >> 4), sld,
+                                   lane, acc);
+        const int row = 16 * rt + (lane & 15), o0 = 16 * nt + 4 * (lane >> 4);
+        if (row < ti.z) {
+            float* out = a.logits + (int64_t)row_slot[row] * a.A;
+            const float* bias = a.b[2] + (int64_t)p * A;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (o0 + e < A)
+                    out[o0 + e] = acc[0][0][e] + bias[o0 + e];
+        }
     }
 }
 
 hipError_t launch_mlp_generic(const Pop& pop, int env_kind, int n_agents, int grid,
                               const int32_t* perm, const int32_t* perm_env,
-                              const int4* tile_info, int max_tiles, int64_t n_slots,
-                              const void* state, float* logits, hipStream_t s)
+                              const int4* tile_info, int max_tiles, int tile_rows,
+                              int64_t n_slots, const void* state, float* logits, hipStream_t s)
 {
     MlpGenericArgs a = {};
+    int widest = 0;
     for (int l = 0; l < 3; ++l) {
         a.w[l] = pop.w[l];
         a.b[l] = pop.b[l];
@@ -1182,8 +1340,15 @@ hipError_t launch_mlp_generic(const Pop& pop, int env_kind, int n_agents, int gr
         a.dims[l] = pop.dims[l];
         if (pop.dims[l] < 1 || pop.dims[l] > kGenericMaxWidth)
             return hipErrorInvalidValue;
+        if (l < 3) {
+            a.kg2[l] = (pop.dims[l] + 31) / 32;
+            widest = std::max(widest, 32 * a.kg2[l]);
+        }
     }
-    a.bf16 = pop.kind == MALIB_POLICY_MLP_BF16;
+    if (pop.A > kMaxActions || max_tiles % 8 != 0 ||
+        (tile_rows != 16 && (tile_rows != 32 || widest > 512)))
+        return hipErrorInvalidValue;
+    a.sld = widest + 4;
     a.perm = perm;
     a.perm_env = perm_env;
     a.tile_info = tile_info;
@@ -1195,24 +1360,53 @@ hipError_t launch_mlp_generic(const Pop& pop, int env_kind, int n_agents, int gr
     a.A = pop.A;
     a.n_envs = n_slots / n_agents;
     a.logits = logits;
-    mlp_generic_kernel<<<max_tiles, kGenericThreads, 0, s>>>(a);
+    auto go = [&](auto kernel) { kernel<<<max_tiles, kGenericThreads, 0, s>>>(a); };
+    const bool r32 = tile_rows == 32;
+    auto pick = [&](auto bf) {
+        constexpr bool BF = decltype(bf)::value;
+        if (widest <= 128)
+            r32 ? go(mlp_generic_kernel<BF, 1, 2>) : go(mlp_generic_kernel<BF, 1, 1>);
+        else if (widest <= 256)
+            r32 ? go(mlp_generic_kernel<BF, 2, 2>) : go(mlp_generic_kernel<BF, 2, 1>);
+        else if (widest <= 512)
+            r32 ? go(mlp_generic_kernel<BF, 4, 2>) : go(mlp_generic_kernel<BF, 4, 1>);
+        else
+            go(mlp_generic_kernel<BF, 8, 1>);
+    };
+    if (pop.kind == MALIB_POLICY_MLP_BF16)
+        pick(std::true_type{});
+    else
+        pick(std::false_type{});
     return hipGetLastError();
 }
 
-// fp32 weights -> bf16 bits (round to nearest even), [n] elements.
-__global__ void round_bf16_kernel(const float* __restrict__ w, int64_t n,
-                                  uint16_t* __restrict__ out)
+// fp32 weights [P][out][in] -> operand order [P][nt][g][lane][j] with element
+// W[16 nt + lane % 16][16 g + 4 j + lane / 16] (g over the inputs padded to 32),
+// fp32 or bf16 bits (round to nearest even), zeros past the edges.
+__global__ void pack_generic_kernel(const float* __restrict__ w, int64_t total, int out, int in,
+                                    int bf16, void* __restrict__ dst)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n)
-        out[i] = bf16_bits(w[i]);
+    if (i >= total)
+        return;
+    const int kgs = (in + 31) / 32 * 2, nts = (out + 15) / 16;
+    const int j = (int)(i & 3), lane = (int)((i >> 2) & 63);
+    const int64_t r = i >> 8;
+    const int g = (int)(r % kgs), nt = (int)((r / kgs) % nts);
+    const int64_t p = r / kgs / nts;
+    const int o = 16 * nt + (lane & 15), c = 16 * g + 4 * j + (lane >> 4);
+    const float v = o < out && c < in ? w[(p * out + o) * in + c] : 0.f;
+    if (bf16)
+        ((uint16_t*)dst)[i] = bf16_bits(v);
+    else
+        ((float*)dst)[i] = v;
 }
 
-hipError_t launch_round_bf16(const float* w, int64_t n, uint16_t* out, hipStream_t s)
+hipError_t launch_pack_generic(const float* w, int P, int out, int in, bool bf16, void* dst,
+                               hipStream_t s)
 {
-    if (n <= 0)
-        return hipSuccess;
-    round_bf16_kernel<<<(int)((n + 255) / 256), 256, 0, s>>>(w, n, out);
+    const int64_t total = (int64_t)P * generic_weight_elems(out, in);
+    pack_generic_kernel<<<(int)((total + 255) / 256), 256, 0, s>>>(w, total, out, in, bf16, dst);
     return hipGetLastError();
 }
 

@@ -95,3 +95,30 @@ def test_generic_extend_equals_create():
     assert np.array_equal(a["counts"], b["counts"])
     m = ~np.isnan(a["mean"])
     assert np.array_equal(a["mean"][m].view(np.uint64), b["mean"][m].view(np.uint64))
+
+
+# hidden widths at the edges of the unit tiles (16), of the pairs of input groups
+# (32), of a wavefront's share (128 per tile) and of the widest tile class
+EDGES = [(1, 1), (15, 17), (16, 33), (31, 32), (127, 129), (128, 257), (255, 511), (513, 24),
+         (1024, 1023)]
+
+
+@pytest.mark.parametrize("kind", [W.MLP_F32, W.MLP_BF16])
+@pytest.mark.parametrize("h1,h2", EDGES)
+def test_generic_width_edges(h1, h2, kind):
+    """Buckets of about 5 to 40 rows (partial and several 16-row tiles)."""
+    wl = W.with_policies(W.team_variant(3, d=64, P=5, n_envs=33, horizon=2), kind,
+                         [64, h1, h2, 18], bias_var=0.02)
+    check_parity(wl, run_gpu(wl, snaps=[0, 1]))
+
+
+@pytest.mark.parametrize("h1,h2", [(100, 60), (130, 256), (512, 300)])
+def test_generic_32_row_tiles(h1, h2):
+    """Batches from 48 rows per CU on take 32-row tiles (widths up to 512)."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    n = 24 * cus + 7
+    wl = W.with_policies(W.team_variant(2, d=64, P=7, n_envs=n, horizon=2), W.MLP_F32,
+                         [64, h1, h2, 18], bias_var=0.02)
+    sel = np.unique(np.concatenate([np.arange(20), np.arange(n - 20, n),
+                                    np.random.default_rng(3).integers(0, n, 60)]))
+    check_parity(wl, run_gpu(wl, snaps=[0, 1]), sel)
