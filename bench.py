@@ -5,7 +5,8 @@ One step = one full pass of the rollout path over one batch: draw every seat's
 policy from the meta-strategy, bucket slots by policy, reset, H x (grouped
 policy forward -> Gumbel-max sampling -> environment step with return
 accumulation), reduce returns into the payoff table and read it back on the
-host.  Inputs (weights, environment parameters, meta-strategy) are resident in
+host.  (Games with few distinct observations evaluate every policy once on each
+of them and then play the H steps from that table.)  Inputs (weights, environment parameters, meta-strategy) are resident in
 HBM before timing starts.
 
 Default workload: the 4v4 team game on R^256 feature dynamics, 16384 envs x 8
@@ -75,35 +76,51 @@ def algorithmic_work(wl):
         d = wl.d
         # state in and out, returns read-modify-write, W and the embedding
         # table once
-        b = n * (8 * d + 8 * na) + 4 * d * d + 4 * na * A * d + 4 * d
-        if wl.pol_kind == W.MLP_BF16 and policy_kernel(wl) == "mlp_bf16_kernel":
+        b = n * (8 * d + 8 * na) + 4 * d * d + 4 * na * A * d + 4 * d + sample
+        if ksample:
             b += n * 2 * d       # the bf16 observation rows for the 64-row kernel
         out["env"] = {"bytes": b, "flops": 2 * d * d * n}
-    elif wl.env_kind == W.PURSUIT:
-        out["env"] = {"bytes": n * (2 * 2 + 1 + 8 * na)}     # cells, done, returns
-    elif wl.env_kind == W.ITER_MATRIX:
-        out["env"] = {"bytes": n * (2 * 2 + 8 * na)}         # history, returns
     else:
-        out["env"] = {"bytes": n * 8 * na}                   # returns
-    out["env"]["bytes"] += sample
+        # the whole horizon in one launch: ids in, returns out
+        out["env"] = {"bytes": 8 * ns}
     if wl.dims:
         wbytes = (2 if wl.pol_kind == W.MLP_BF16 else 4) * wl.P * sum(
             wl.dims[i] * wl.dims[i + 1] for i in range(len(wl.dims) - 1))
         # feature observations, each env's once: fp32 state rows for the
-        # persistent kernel, the env step's bf16 rows for the 64-row kernel
+        # persistent kernel, the env step's bf16 rows for the 64-row kernel;
+        # elsewhere the table of logits is written
         obs = 0
         if wl.env_kind == W.FEATURE:
-            obs = n * wl.d * (4 if policy_kernel(wl) == "mlp_bf16_persist_kernel" else 2)
-        out["policy"] = {"bytes": wbytes + obs + sample,
-                         "flops": policy_flops_per_frame(wl.dims) * ns}
-    else:
-        out["policy"] = {"bytes": wl.P * A * 4 + ns * 4 * A}
+            obs = n * wl.d * (4 if policy_kernel(wl) == "mlp_bf16_persist_kernel" else 2) + sample
+        else:
+            obs = 4 * A * policy_rows(wl)
+        out["policy"] = {"bytes": wbytes + obs,
+                         "flops": policy_flops_per_frame(wl.dims) * policy_rows(wl)}
     # payoff reduction, once per fill: every seat's int32 policy id and each
     # row-side seat's fp32 return read once, the table's three accumulators
     # (sum, sum of squares: int64; count: uint32) updated once per cell
     n_row = int((wl.team > 0).sum())
     out["payoff"] = {"bytes": ns * 4 + n * n_row * 4 + wl.P * wl.P * 20}
     return out
+
+
+def one_launch(wl):
+    """Games with few distinct observations: the library evaluates each policy
+    once on every observation and plays the whole horizon in one launch."""
+    import workloads as W
+    return wl.env_kind != W.FEATURE
+
+
+def policy_rows(wl):
+    """Rows of one policy-forward launch: every slot of a step, or, for the
+    iterated game and pursuit, every policy's distinct observations (histories
+    of up to four joint actions; 26 relative places for each of two seats)."""
+    import workloads as W
+    if wl.env_kind == W.ITER_MATRIX:
+        return wl.P * sum((wl.n_actions ** 2) ** k for k in range(min(wl.horizon, 5)))
+    if wl.env_kind == W.PURSUIT:
+        return wl.P * 52
+    return wl.n_envs * wl.n_agents
 
 
 def policy_kernel(wl):
@@ -535,7 +552,7 @@ def main():
     # timed region: HIP events around one grouped-forward launch in `every`
     # (about 16 per fill): the events' own cost shows up in the fill time, by
     # ~1% on the 4v4 game and ~2% on pursuit at one launch in four
-    every = args.event_every or max(4, wl.horizon // 16)
+    every = args.event_every or (1 if one_launch(wl) else max(4, wl.horizon // 16))
     pop.profile_enable(True, kernels=[M.K_POLICY], every=every)
     frames = 0
     torch.cuda.synchronize()
@@ -556,12 +573,11 @@ def main():
     pop.profile_enable(True)
     one_step()
     work = algorithmic_work(wl)
-    # per step for the policy forward and the env step, per fill for set-up
-    # and payoff
+    # per step for the feature games' policy forward and env step, else per fill
     for name, k in (("policy", M.K_POLICY), ("env", M.K_ENV), ("setup", M.K_SETUP),
                     ("payoff", M.K_PAYOFF)):
         ms, cnt = pop.profile_read(k)
-        per = wl.horizon if name in ("policy", "env") else 1
+        per = wl.horizon if name in ("policy", "env") and not one_launch(wl) else 1
         kern[name] = {"total_ms": round(ms, 3), "launches": cnt,
                       "avg_us": round(1000.0 * ms / max(cnt, 1), 3),
                       "per_step_us" if per > 1 else "per_fill_us": round(1000.0 * ms / per, 3)}
@@ -591,7 +607,7 @@ def main():
         bf16 = wl.pol_kind == W.MLP_BF16
         peak = PEAK_BF16_TFLOPS if bf16 else PEAK_F32_MFMA_TFLOPS
         kname = policy_kernel(wl) if bf16 else "mlp_f32_kernel"
-        flops = policy_flops_per_frame(wl.dims) * n * na        # per launch
+        flops = policy_flops_per_frame(wl.dims) * policy_rows(wl)   # per launch
         avg_s = policy_avg_us * 1e-6
         ach = flops / avg_s / 1e12
         # the committed counters are per launch of the configuration's batch

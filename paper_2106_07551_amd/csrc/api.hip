@@ -592,6 +592,13 @@ struct RolloutPlan {
     bool striped = false;         // tile table in XCD segments (64-row and generic kernels)
     int tile_rows = 0, max_tiles = 0, n_chunks = 0;
     int64_t state_bytes = 0;      // one state buffer (FEATURE has two)
+    // games with few distinct observations: the policies' logits on all of them
+    // once (table, nothing to do for tabular policies), then the whole horizon
+    // in one kernel
+    bool finite = false;
+    int rows = 1, row_seats = 1;  // table entries per policy, slots per entry
+    int t_tile_rows = 0, t_entries = 0;   // tiles of the table's forward
+    bool t_striped = false;
 };
 
 // Device buffers of one rollout batch (from the handle, or carved from the
@@ -728,6 +735,29 @@ static malib_status plan_rollout(malib_pop_t pop, const malib_env_desc* env, int
     // kernel (its noise is drawn while the observation rows are fetched), so
     // the env step only reads one action byte per slot
     plan.kernel_sample = plan.bf16_obs;
+    if (env->kind != MALIB_ENV_FEATURE) {
+        plan.finite = true;
+        if (plan.mlp) {
+            const bool f32 = pop->kind == MALIB_POLICY_MLP_F32 && !pop->generic;
+            plan.rows = finite_rows(env->kind, pop->A, horizon);
+            plan.row_seats = env->kind == MALIB_ENV_PURSUIT ? 2 : 1;
+            const int64_t tns = (int64_t)pop->P * plan.rows * plan.row_seats;
+            plan.t_tile_rows = pop->generic ? generic_tile_rows(pop->dims, tns, pop->n_cus)
+                               : f32 ? kF32TileRows : kBf16TileRows;
+            plan.t_striped = !f32;
+            plan.t_entries = plan.t_striped ? striped_entries(tns, pop->P, plan.t_tile_rows)
+                                            : max_tiles_for(tns, pop->P, plan.t_tile_rows);
+            // worth it unless the table is more work than the steps' own
+            // evaluations; a step by itself costs two launches, some 10 us, in
+            // which a forward does about 4e8 operations
+            const double per_row = 2.0 * ((double)pop->dims[0] * pop->dims[1] +
+                                          (double)pop->dims[1] * pop->dims[2] +
+                                          (double)pop->dims[2] * pop->dims[3]);
+            plan.finite = tns <= ((int64_t)1 << 26) &&
+                          per_row * (double)tns <=
+                              horizon * std::max(per_row * (double)ns, 4e8);
+        }
+    }
     return MALIB_OK;
 }
 
@@ -755,6 +785,45 @@ static void buffer_sizes(const Pop& pop, const malib_env_desc* env, int64_t n_en
     sz[14] = plan.kernel_sample ? (size_t)ns : 0;                        // actions
 }
 
+// The same for a finite plan without trace: the returns, the table with its
+// virtual batch, and what the payoff reduction of large populations needs.
+static void finite_buffer_sizes(const Pop& pop, int64_t n_envs, const RolloutPlan& plan,
+                                size_t (&sz)[kNumBufs])
+{
+    const int64_t ns = plan.ns, tenvs = (int64_t)pop.P * plan.rows, tns = tenvs * plan.row_seats;
+    for (size_t& x : sz)
+        x = 0;
+    sz[1] = sizeof(float) * ns;                                          // ret
+    if (!plan.mlp)
+        return;
+    const bool bucket = !payoff_stream_fits(pop.P);
+    const size_t pc = bucket ? (size_t)pop.P * plan.n_chunks : 0;
+    sz[0] = sizeof(float) * tns * pop.A;                                 // logits: the table
+    sz[3] = 2 * (size_t)tenvs;                                           // state1: its envs
+    sz[7] = sizeof(int32_t) * std::max(tns, bucket ? ns : 0);            // perm
+    sz[8] = sz[7];                                                       // perm_env
+    sz[9] = sizeof(int32_t) * pc;                                        // hist
+    sz[10] = sizeof(int32_t) * pc;                                       // base
+    sz[11] = sizeof(int32_t) * (pop.P + 1);                              // offsets
+    sz[12] = sizeof(int32_t) * (pop.P + 1);                              // tile_off
+    sz[13] = sizeof(int4) * (size_t)std::max(plan.t_entries, bucket ? plan.max_tiles : 0);
+    (void)n_envs;
+}
+
+// What the handle keeps for a batch: room for both ways of playing it, so that
+// which of them a later batch takes does not matter to a capture.
+static void handle_sizes(const Pop& pop, const malib_env_desc* env, int64_t n_envs,
+                         const RolloutPlan& plan, size_t (&sz)[kNumBufs])
+{
+    buffer_sizes(pop, env, n_envs, plan, sz);
+    if (plan.finite) {
+        size_t fz[kNumBufs];
+        finite_buffer_sizes(pop, n_envs, plan, fz);
+        for (int i = 0; i < kNumBufs; ++i)
+            sz[i] = std::max(sz[i], fz[i]);
+    }
+}
+
 static void assign_bufs(void* const (&ptr)[kNumBufs], RolloutBufs& b)
 {
     b.logits = (float*)ptr[0];
@@ -779,7 +848,7 @@ static bool handle_bufs_fit(const Pop& pop, const malib_env_desc* env, int64_t n
                             const RolloutPlan& plan)
 {
     size_t sz[kNumBufs];
-    buffer_sizes(pop, env, n_envs, plan, sz);
+    handle_sizes(pop, env, n_envs, plan, sz);
     const DevBuf* db[kNumBufs] = {&pop.logits, &pop.ret, &pop.state0, &pop.state1, &pop.done,
                                   &pop.wt, &pop.obs, &pop.perm, &pop.perm_env, &pop.hist,
                                   &pop.base, &pop.offsets, &pop.tile_off, &pop.tile_info,
@@ -795,7 +864,7 @@ static malib_status handle_bufs(malib_pop_t pop, const malib_env_desc* env, int6
                                 const RolloutPlan& plan, RolloutBufs& b)
 {
     size_t sz[kNumBufs];
-    buffer_sizes(*pop, env, n_envs, plan, sz);
+    handle_sizes(*pop, env, n_envs, plan, sz);
     DevBuf* db[kNumBufs] = {&pop->logits, &pop->ret, &pop->state0, &pop->state1, &pop->done,
                       &pop->wt, &pop->obs, &pop->perm, &pop->perm_env, &pop->hist,
                       &pop->base, &pop->offsets, &pop->tile_off, &pop->tile_info,
@@ -850,79 +919,155 @@ static malib_status launch_rollout(malib_pop_t pop, const malib_env_desc* env, i
             prof_end(*pop, i, s);
     };
 
-    // ---- set-up: returns cleared (a fill kernel, no memset), bucketing, reset
-    int pi = pbeg(MALIB_K_SETUP);
-    HIP_TRY(launch_zero_f32(ret, ns, s));
-    if (mlp)
-        HIP_TRY(launch_bucket(pair_assign, ns, n_agents, pop->P, plan.tile_rows, plan.max_tiles,
-                              plan.striped, b.hist, b.base, b.perm, b.perm_env, b.offsets,
-                              b.tile_off, b.tile_info, pop->dev_flags, s));
-    HIP_TRY(launch_reset(ea, n_envs, seed, env_offset, cur, done, s));
-    if (env->kind == MALIB_ENV_FEATURE)
-        HIP_TRY(launch_pack_dynamics(env->W, b.wt, env->d, s));
-    pend(pi);
-    if (trace && mlp) {
-        if (trace->perm)
-            HIP_TRY(hipMemcpyAsync(trace->perm, b.perm, sizeof(int32_t) * ns,
-                                   hipMemcpyDeviceToDevice, s));
-        if (trace->offsets)
-            HIP_TRY(hipMemcpyAsync(trace->offsets, b.offsets, sizeof(int32_t) * (pop->P + 1),
-                                   hipMemcpyDeviceToDevice, s));
-    }
-
-    // ---- the step loop
+    auto bucket = [&]() {
+        return launch_bucket(pair_assign, ns, n_agents, pop->P, plan.tile_rows, plan.max_tiles,
+                             plan.striped, b.hist, b.base, b.perm, b.perm_env, b.offsets,
+                             b.tile_off, b.tile_info, pop->dev_flags, s);
+    };
+    auto trace_buckets = [&]() {
+        hipError_t e = hipSuccess;
+        if (trace && mlp && trace->perm)
+            e = hipMemcpyAsync(trace->perm, b.perm, sizeof(int32_t) * ns,
+                               hipMemcpyDeviceToDevice, s);
+        if (e == hipSuccess && trace && mlp && trace->offsets)
+            e = hipMemcpyAsync(trace->offsets, b.offsets, sizeof(int32_t) * (pop->P + 1),
+                               hipMemcpyDeviceToDevice, s);
+        return e;
+    };
     const int64_t snap_b = snap_bytes_per_env(env->kind, env->d) * n_envs;
-    for (int t = 0; t < horizon; ++t) {
-        const int si = snap_of ? snap_of[t] : -1;
-        if (si >= 0 && trace->states && snap_b > 0) {
-            uint8_t* dst = (uint8_t*)trace->states + (int64_t)si * snap_b;
-            if (env->kind == MALIB_ENV_PURSUIT)
-                HIP_TRY(launch_snapshot_pursuit(cur, done, n_envs, dst, s));
+    auto snap_state = [&](int si) {
+        uint8_t* dst = (uint8_t*)trace->states + (int64_t)si * snap_b;
+        return env->kind == MALIB_ENV_PURSUIT
+                   ? launch_snapshot_pursuit(cur, done, n_envs, dst, s)
+                   : hipMemcpyAsync(dst, cur, snap_b, hipMemcpyDeviceToDevice, s);
+    };
+    int pi;
+    if (plan.finite) {
+        // ---- few distinct observations: the table, then the whole horizon
+        const bool traced = trace && (snap_of || trace->perm || trace->offsets);
+        const float* table = pop->tab;
+        if (mlp) {
+            const int64_t tns = (int64_t)pop->P * plan.rows * plan.row_seats;
+            pi = pbeg(MALIB_K_SETUP);
+            HIP_TRY(launch_finite_table(env->kind, pop->A, env->grid, pop->P, plan.rows,
+                                        plan.row_seats, plan.t_tile_rows, plan.t_entries,
+                                        plan.t_striped, b.state1, b.perm, b.perm_env,
+                                        b.tile_info, s));
+            pend(pi);
+            pi = pbeg(MALIB_K_POLICY);
+            if (pop->generic)
+                HIP_TRY(launch_mlp_generic(*pop, env->kind, plan.row_seats, env->grid, b.perm,
+                                           b.perm_env, b.tile_info, plan.t_entries,
+                                           plan.t_tile_rows, tns, b.state1, logits, s));
+            else if (pop->kind == MALIB_POLICY_MLP_F32)
+                HIP_TRY(launch_mlp_f32(*pop, b.perm, b.tile_info, tns, plan.row_seats, b.state1,
+                                       logits, s));
             else
-                HIP_TRY(hipMemcpyAsync(dst, cur, snap_b, hipMemcpyDeviceToDevice, s));
+                HIP_TRY(launch_mlp_bf16(*pop, env->kind, plan.row_seats, env->grid, env->d,
+                                        plan.t_tile_rows, b.perm, b.perm_env, b.tile_info, tns,
+                                        b.state1, logits, nullptr, s));
+            pend(pi);
+            table = logits;
         }
-        pi = pbeg(MALIB_K_POLICY);
-        if (pop->kind == MALIB_POLICY_TABULAR)
-            HIP_TRY(launch_tabular(pop->tab, pair_assign, ns, pop->A, pop->P, pop->dev_flags,
-                                   logits, s));
-        else if (pop->generic)
-            HIP_TRY(launch_mlp_generic(*pop, env->kind, n_agents, env->grid, b.perm, b.perm_env,
-                                       b.tile_info, plan.max_tiles, plan.tile_rows, ns, cur, logits,
-                                       s));
-        else if (pop->kind == MALIB_POLICY_MLP_F32)
-            HIP_TRY(launch_mlp_f32(*pop, b.perm, b.tile_info, ns, n_agents, cur, logits, s));
-        else if (persist)
-            HIP_TRY(launch_mlp_bf16_persist(*pop, b.perm, b.perm_env, b.tile_info, b.tile_off,
-                                            ns, n_agents, cur, logits, s));
-        else
-        {
-            KernelSample ks{b.actions, pop->dev_flags, seed, env_offset, t};
-            // the logits are written only when a trace snapshot reads them
-            float* lg = plan.kernel_sample && !(si >= 0 && trace->logits) ? nullptr : logits;
-            HIP_TRY(launch_mlp_bf16(*pop, env->kind, n_agents, env->grid, env->d,
-                                    plan.tile_rows, b.perm, b.perm_env, b.tile_info, ns,
-                                    plan.bf16_obs ? (const void*)ea.obs : cur, lg,
-                                    plan.kernel_sample ? &ks : nullptr, s));
+        FiniteLaunch fl = {};
+        fl.env = ea;
+        fl.table = table;
+        fl.rows = plan.rows;
+        fl.per_seat = mlp && plan.row_seats == 2;
+        fl.pids = pair_assign;
+        fl.P = pop->P;
+        fl.n_envs = n_envs;
+        fl.env_offset = env_offset;
+        fl.seed = seed;
+        fl.log = trace ? trace->actions : nullptr;
+        fl.state = cur;
+        fl.done = done;
+        fl.ret = ret;
+        fl.frames = pop->dev_frames;
+        fl.flags = pop->dev_flags;
+        if (traced)   // snapshots before the first step read the state
+            HIP_TRY(launch_reset(ea, n_envs, seed, env_offset, cur, done, s));
+        for (int t = 0; t < horizon;) {
+            const int si = snap_of ? snap_of[t] : -1;
+            if (si >= 0 && trace->states && snap_b > 0)
+                HIP_TRY(snap_state(si));
+            if (si >= 0 && trace->logits)
+                HIP_TRY(launch_finite_logits(fl, trace->logits + (int64_t)si * ns * pop->A, s));
+            fl.t0 = t;
+            for (++t; t < horizon && !(snap_of && snap_of[t] >= 0); ++t) {
+            }
+            fl.t1 = t;
+            fl.keep = traced;
+            pi = pbeg(MALIB_K_ENV);
+            HIP_TRY(launch_finite(fl, s));
+            pend(pi);
         }
+        if (mlp && (!payoff_stream_fits(pop->P) || traced)) {
+            pi = pbeg(MALIB_K_SETUP);
+            HIP_TRY(bucket());
+            pend(pi);
+            HIP_TRY(trace_buckets());
+        }
+    } else {
+        // ---- set-up: returns cleared (a fill kernel, no memset), bucketing, reset
+        pi = pbeg(MALIB_K_SETUP);
+        HIP_TRY(launch_zero_f32(ret, ns, s));
+        if (mlp)
+            HIP_TRY(bucket());
+        HIP_TRY(launch_reset(ea, n_envs, seed, env_offset, cur, done, s));
+        if (env->kind == MALIB_ENV_FEATURE)
+            HIP_TRY(launch_pack_dynamics(env->W, b.wt, env->d, s));
         pend(pi);
-        if (si >= 0 && trace->logits)
-            HIP_TRY(hipMemcpyAsync(trace->logits + (int64_t)si * ns * pop->A, logits,
-                                   sizeof(float) * ns * pop->A, hipMemcpyDeviceToDevice, s));
-        // action sampling happens inside the env step (one launch fewer per step)
-        SampleArgs sa;
-        sa.logits = logits;
-        sa.seed = seed;
-        sa.env_offset = env_offset;
-        sa.t = t;
-        sa.log = (trace && trace->actions) ? trace->actions + (int64_t)t * ns : nullptr;
-        sa.flags = pop->dev_flags;
-        sa.actions = plan.kernel_sample ? b.actions : nullptr;
-        pi = pbeg(MALIB_K_ENV);
-        HIP_TRY(launch_env_step(ea, sa, n_envs, cur, nxt, done, ret, pop->dev_frames, s));
-        pend(pi);
-        std::swap(cur, nxt);
-        if (env->kind != MALIB_ENV_FEATURE)
-            nxt = cur;
+        HIP_TRY(trace_buckets());
+
+        // ---- the step loop
+        for (int t = 0; t < horizon; ++t) {
+            const int si = snap_of ? snap_of[t] : -1;
+            if (si >= 0 && trace->states && snap_b > 0)
+                HIP_TRY(snap_state(si));
+            pi = pbeg(MALIB_K_POLICY);
+            if (pop->kind == MALIB_POLICY_TABULAR)
+                HIP_TRY(launch_tabular(pop->tab, pair_assign, ns, pop->A, pop->P, pop->dev_flags,
+                                       logits, s));
+            else if (pop->generic)
+                HIP_TRY(launch_mlp_generic(*pop, env->kind, n_agents, env->grid, b.perm, b.perm_env,
+                                           b.tile_info, plan.max_tiles, plan.tile_rows, ns, cur, logits,
+                                           s));
+            else if (pop->kind == MALIB_POLICY_MLP_F32)
+                HIP_TRY(launch_mlp_f32(*pop, b.perm, b.tile_info, ns, n_agents, cur, logits, s));
+            else if (persist)
+                HIP_TRY(launch_mlp_bf16_persist(*pop, b.perm, b.perm_env, b.tile_info, b.tile_off,
+                                                ns, n_agents, cur, logits, s));
+            else
+            {
+                KernelSample ks{b.actions, pop->dev_flags, seed, env_offset, t};
+                // the logits are written only when a trace snapshot reads them
+                float* lg = plan.kernel_sample && !(si >= 0 && trace->logits) ? nullptr : logits;
+                HIP_TRY(launch_mlp_bf16(*pop, env->kind, n_agents, env->grid, env->d,
+                                        plan.tile_rows, b.perm, b.perm_env, b.tile_info, ns,
+                                        plan.bf16_obs ? (const void*)ea.obs : cur, lg,
+                                        plan.kernel_sample ? &ks : nullptr, s));
+            }
+            pend(pi);
+            if (si >= 0 && trace->logits)
+                HIP_TRY(hipMemcpyAsync(trace->logits + (int64_t)si * ns * pop->A, logits,
+                                       sizeof(float) * ns * pop->A, hipMemcpyDeviceToDevice, s));
+            // action sampling happens inside the env step (one launch fewer per step)
+            SampleArgs sa;
+            sa.logits = logits;
+            sa.seed = seed;
+            sa.env_offset = env_offset;
+            sa.t = t;
+            sa.log = (trace && trace->actions) ? trace->actions + (int64_t)t * ns : nullptr;
+            sa.flags = pop->dev_flags;
+            sa.actions = plan.kernel_sample ? b.actions : nullptr;
+            pi = pbeg(MALIB_K_ENV);
+            HIP_TRY(launch_env_step(ea, sa, n_envs, cur, nxt, done, ret, pop->dev_frames, s));
+            pend(pi);
+            std::swap(cur, nxt);
+            if (env->kind != MALIB_ENV_FEATURE)
+                nxt = cur;
+        }
     }
 
     // ---- payoff reduction
@@ -977,6 +1122,9 @@ static malib_status rollout_impl(malib_pop_t pop, const malib_env_desc* env, int
     HIP_TRY(hipStreamIsCapturing(s, &cap));
     // growing a buffer synchronizes the device and frees memory, which a
     // capture in progress does not allow
+    if (cap != hipStreamCaptureStatusNone && plan.finite &&
+        !handle_bufs_fit(*pop, env, n_envs, plan))
+        plan.finite = !plan.mlp;   // step by step, if that fits
     if (cap != hipStreamCaptureStatusNone && !handle_bufs_fit(*pop, env, n_envs, plan))
         return fail(MALIB_E_INVAL,
                     "the stream is being captured and this batch needs larger device buffers "
@@ -1090,17 +1238,30 @@ malib_status malib_rollout_batch_noalloc(malib_pop_t pop, const malib_env_desc* 
                     hipGetErrorString(e));
     }
     size_t sz[kNumBufs];
-    buffer_sizes(*pop, env, n_envs, plan, sz);
     void* ptr[kNumBufs];
     size_t off = 0;
-    for (int i = 0; i < kNumBufs; ++i) {
-        ptr[i] = nullptr;
-        if (sz[i]) {
-            ptr[i] = (unsigned char*)pop->scratch + off;
-            off += (sz[i] + 255) / 256 * 256;
+    auto carve = [&]() {
+        off = 0;
+        for (int i = 0; i < kNumBufs; ++i) {
+            ptr[i] = nullptr;
+            if (sz[i]) {
+                ptr[i] = (unsigned char*)pop->scratch + off;
+                off += (sz[i] + 255) / 256 * 256;
+            }
         }
+        return off <= kNoAllocScratchBytes;
+    };
+    bool fits = false;
+    if (plan.finite) {
+        finite_buffer_sizes(*pop, n_envs, plan, sz);
+        fits = carve();
     }
-    if (off > kNoAllocScratchBytes)
+    if (!fits) {   // step by step
+        plan.finite = false;
+        buffer_sizes(*pop, env, n_envs, plan, sz);
+        fits = carve();
+    }
+    if (!fits)
         return fail(MALIB_E_INVAL,
                     "the batch needs %zu bytes of scratch, above the %zu bytes of "
                     "malib_rollout_batch_noalloc (use malib_rollout_batch)",

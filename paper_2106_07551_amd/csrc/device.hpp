@@ -34,24 +34,32 @@ __device__ __forceinline__ void mul_hilo64(uint64_t a, uint64_t b, uint64_t& lo,
     hi = (uint64_t)a1 * b1 + ((t >> 32) + (u >> 32));
 }
 
-__device__ __forceinline__ u64x4 philox4x64_10(u64x4 c, uint64_t k0, uint64_t k1)
+constexpr uint64_t kPhiloxM0 = 0xD2E7470EE14C6C93ull, kPhiloxM1 = 0xCA5A826395121157ull;
+constexpr uint64_t kPhiloxW0 = 0x9E3779B97F4A7C15ull, kPhiloxW1 = 0xBB67AE8584CAA73Bull;
+
+template <int ROUNDS>
+__device__ __forceinline__ u64x4 philox_rounds(u64x4 c, uint64_t k0, uint64_t k1)
 {
 #pragma unroll
-    for (int r = 0; r < 10; ++r) {
-        const uint64_t m0 = 0xD2E7470EE14C6C93ull, m1 = 0xCA5A826395121157ull;
+    for (int r = 0; r < ROUNDS; ++r) {
         uint64_t lo0, hi0, lo1, hi1;
-        mul_hilo64(m0, c.x, lo0, hi0);
-        mul_hilo64(m1, c.z, lo1, hi1);
+        mul_hilo64(kPhiloxM0, c.x, lo0, hi0);
+        mul_hilo64(kPhiloxM1, c.z, lo1, hi1);
         u64x4 n;
         n.x = hi1 ^ c.y ^ k0;
         n.y = lo1;
         n.z = hi0 ^ c.w ^ k1;
         n.w = lo0;
         c = n;
-        k0 += 0x9E3779B97F4A7C15ull;
-        k1 += 0xBB67AE8584CAA73Bull;
+        k0 += kPhiloxW0;
+        k1 += kPhiloxW1;
     }
     return c;
+}
+
+__device__ __forceinline__ u64x4 philox4x64_10(u64x4 c, uint64_t k0, uint64_t k1)
+{
+    return philox_rounds<10>(c, k0, k1);
 }
 
 // The block of the stream at (global env g, step t, purpose, slot, block):
@@ -206,6 +214,14 @@ __device__ __forceinline__ int gumbel_action(const float* __restrict__ l, int A,
     }
     nan = bad;
     return bad ? 0 : best;
+}
+
+// LDS written by this wavefront becomes visible to its other lanes.
+__device__ __forceinline__ void wave_lds_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 }  // namespace malib

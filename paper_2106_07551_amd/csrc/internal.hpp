@@ -298,6 +298,33 @@ hipError_t launch_mlp_bf16_persist(const Pop& pop, const int32_t* perm, const in
                                    int64_t n_slots, int n_agents, const void* state,
                                    float* logits, hipStream_t s);
 
+// Games with few distinct observations (k_finite.hip): the table's entries per
+// policy, the virtual batch that evaluates them (seats slots per entry, sorted by
+// policy), and the whole horizon in one kernel (steps t0 .. t1 - 1; the state
+// and returns start anew at t0 = 0, else from what a launch with keep left).
+int finite_rows(int env_kind, int A, int horizon);
+hipError_t launch_finite_table(int env_kind, int A, int grid, int P, int rows, int seats,
+                               int tile_rows, int n_entries, bool striped, void* state,
+                               int32_t* perm, int32_t* perm_env, int4* info, hipStream_t s);
+struct FiniteLaunch {
+    EnvArgs env;
+    const float* table;      // [P][rows][A], or [P][rows][2][A] with per_seat
+    int rows, per_seat;
+    const int32_t* pids;
+    int P;
+    int64_t n_envs, env_offset;
+    uint64_t seed;
+    int t0, t1, keep;
+    uint8_t* log;            // [horizon][n_slots], or null
+    void* state;
+    uint8_t* done;
+    float* ret;
+    unsigned long long* frames;
+    int* flags;
+};
+hipError_t launch_finite(const FiniteLaunch& L, hipStream_t s);
+hipError_t launch_finite_logits(const FiniteLaunch& L, float* out, hipStream_t s);
+
 // Diagnostics.
 hipError_t launch_debug_bf16(const float* x, uint16_t* y, int64_t n, hipStream_t s);
 hipError_t launch_debug_tanh(const float* x, float* y, int64_t n, hipStream_t s);

@@ -130,7 +130,7 @@ hipError_t launch_pack_dynamics(const float* W, float* WP, int d, hipStream_t s)
     return hipGetLastError();
 }
 
-// ---------------------------------------------------- matrix / iterated / pursuit
+// ------------------------------- iterated game and pursuit, step by step
 
 // The two seats' actions of env e (Gumbel-max over their logits, logged when
 // asked); a NaN logit raises kErrNaN.
@@ -150,31 +150,29 @@ __device__ __forceinline__ void sample_pair(const SampleArgs& sa, int A, int64_t
     }
 }
 
-// One thread per env: both seats' actions, then MATRIX and ITER_MATRIX:
-// r0 = A[a0][a1], r1 = -r0; ITER also shifts the joint action into its history.
-template <int AMAX>
-__global__ void step_matrix_kernel(const float* __restrict__ Amat, int A, int iter, int64_t n,
-                                   SampleArgs sa, TrajArgs tr, uint16_t* __restrict__ hist,
-                                   float* __restrict__ ret)
+// Iterated game, one thread per env: both seats' actions (at most 3), r0 =
+// A[a0][a1], r1 = -r0, the joint action shifted into the history.
+__global__ void step_iter_kernel(const float* __restrict__ Amat, int A, int64_t n, SampleArgs sa,
+                                 TrajArgs tr, uint16_t* __restrict__ hist,
+                                 float* __restrict__ ret)
 {
     int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= n)
         return;
     int a0, a1;
-    sample_pair<AMAX>(sa, A, e, a0, a1);
+    sample_pair<8>(sa, A, e, a0, a1);
     float v = Amat[a0 * A + a1];
     ret[e] = ret[e] + v;
     ret[n + e] = ret[n + e] + (-v);
-    const uint32_t h = iter ? hist[e] : 0u;
-    if (iter)
-        hist[e] = (uint16_t)(((h << 4) | (uint32_t)(a0 * 3 + a1)) & 0xFFFFu);
+    const uint32_t h = hist[e];
+    hist[e] = (uint16_t)(((h << 4) | (uint32_t)(a0 * 3 + a1)) & 0xFFFFu);
     if (tr.act) {
         const int64_t r = traj_rec(tr, sa.t, n, e);
         tr.act[2 * r] = (uint8_t)a0;
         tr.act[2 * r + 1] = (uint8_t)a1;
         tr.rew[r] = v;
         tr.flags[r] = sa.t == tr.horizon - 1 ? 2 : 0;
-        if (iter && tr.obs)
+        if (tr.obs)
             ((uint16_t*)tr.obs)[r] = (uint16_t)h;
     }
 }
@@ -494,14 +492,6 @@ __device__ __forceinline__ void feat_store_acc(float* Ss, int mw, int tx,
                                       16 * (mw * T::NTW + i) + 4 * (tx >> 4)) = acc[i][r];
 }
 
-// LDS written by this wavefront becomes visible to its other lanes.
-__device__ __forceinline__ void wave_lds_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // The actions of epilogue wavefront ew's envs -> act (bytes [EPW][kMaxAgents]):
 // read where the policy kernel sampled them, else Gumbel-max over the slot's
 // logits, four lanes per slot, lane b taking Philox block b (actions 8b .. 8b+7);
@@ -736,22 +726,12 @@ hipError_t launch_env_step(const EnvArgs& e, const SampleArgs& sa, int64_t n_env
 {
     int blocks = (int)((n_envs + 255) / 256);
     switch (e.kind) {
-    case MALIB_ENV_MATRIX:
-    case MALIB_ENV_ITER_MATRIX: {
-        const int iter = e.kind == MALIB_ENV_ITER_MATRIX;
-        uint16_t* hist = iter ? (uint16_t*)state_out : nullptr;
-        if (e.A <= 8)
-            step_matrix_kernel<8><<<blocks, 256, 0, s>>>(e.Amat, e.A, iter, n_envs, sa, e.tr, hist, ret);
-        else if (e.A <= 16)
-            step_matrix_kernel<16><<<blocks, 256, 0, s>>>(e.Amat, e.A, iter, n_envs, sa, e.tr, hist, ret);
-        else if (e.A <= 24)
-            step_matrix_kernel<24><<<blocks, 256, 0, s>>>(e.Amat, e.A, iter, n_envs, sa, e.tr, hist, ret);
-        else if (e.A <= 32)
-            step_matrix_kernel<32><<<blocks, 256, 0, s>>>(e.Amat, e.A, iter, n_envs, sa, e.tr, hist, ret);
-        else
+    case MALIB_ENV_ITER_MATRIX:
+        if (e.A > 3)
             return hipErrorInvalidValue;
+        step_iter_kernel<<<blocks, 256, 0, s>>>(e.Amat, e.A, n_envs, sa, e.tr,
+                                                (uint16_t*)state_out, ret);
         break;
-    }
     case MALIB_ENV_PURSUIT:
         if (e.A != 5)
             return hipErrorInvalidValue;

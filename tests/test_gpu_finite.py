@@ -1,0 +1,181 @@
+"""Games with few distinct observations (matrix, iterated game, pursuit): the
+table of logits and the kernel that plays the whole horizon from it, at the
+sizes where they can go wrong, against the oracle (gpu_helpers.check_parity:
+logits, states, actions and returns) and against the step-by-step route."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+import workloads as W
+from gpu_helpers import check_parity, run_gpu, say
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+def _same(a, b):
+    """Returns and table of two runs of the same batch, bit for bit."""
+    assert np.array_equal(a["returns"].view(np.uint32), b["returns"].view(np.uint32))
+    for k in ("counts", "live_frames", "envs"):
+        assert np.array_equal(a["table"][k], b["table"][k])
+    m = a["table"]["counts"] > 0
+    assert np.array_equal(a["table"]["mean"][m].view(np.uint64),
+                          b["table"]["mean"][m].view(np.uint64))
+
+
+def _check(wl, sel=None, snaps=(0,), pairs=None):
+    """The traced run against the oracle, the untraced one against the traced."""
+    g = run_gpu(wl, snaps=snaps, pairs=pairs)
+    check_parity(wl, g, sel)
+    _same(run_gpu(wl, trace=False, pairs=pairs), g)
+
+
+# one env; the last and the first batch of each number of lanes per env
+SIZES = [1, 3, 4096, 4097, 24576, 24577]
+
+
+@pytest.mark.parametrize("n", SIZES)
+def test_pursuit_batch_sizes(n):
+    wl = W.with_policies(W.make(3, P=5, n_envs=n, horizon=21), W.MLP_BF16, [75, 64, 64, 5],
+                         bias_var=0.02)
+    sel = np.unique(np.r_[0, n // 2, n - 1, np.random.default_rng(n).integers(0, n, 60)])
+    _check(wl, sel, snaps=[0, 1, 16, 17, 20], pairs=W.random_pairs(5, n, 2))
+
+
+@pytest.mark.parametrize("n", SIZES)
+def test_iter_batch_sizes(n):
+    wl = dataclasses.replace(W.make(2, P=3, per_pair=1, horizon=19), n_envs=n)
+    sel = np.unique(np.r_[0, n // 2, n - 1, np.random.default_rng(n).integers(0, n, 60)])
+    _check(wl, sel, snaps=[0, 3, 4, 5, 18], pairs=W.random_pairs(3, n, 2))
+
+
+@pytest.mark.parametrize("horizon", [1, 2, 3, 4, 5, 6])
+def test_iter_histories(horizon):
+    """Every length of history."""
+    _check(W.with_policies(W.make(2, P=4, per_pair=5, horizon=horizon), W.MLP_F32,
+                           [24, 20, 12, 3], bias_var=0.05), snaps=list(range(horizon)))
+
+
+def _policies(wl, P):
+    """The same workload with its first policies repeated up to P of them."""
+    pick = np.arange(P) % wl.P
+    return dataclasses.replace(wl, P=P, weights=[w[pick] for w in wl.weights],
+                               biases=[b[pick] for b in wl.biases])
+
+
+@pytest.mark.parametrize("horizon", [2, 5, 9])
+@pytest.mark.parametrize("actions", [1, 2])
+def test_iter_fewer_actions(actions, horizon):
+    """One or two actions, which the oracle does not play: the traced run, the
+    untraced one and (two actions) the step-by-step route of 256 wide policies."""
+    base = W.make(2, P=3, per_pair=1, horizon=horizon)
+    wl = dataclasses.replace(base, n_actions=actions, n_envs=70,
+                             A=np.ascontiguousarray(base.A[-actions:, -actions:]))
+    wl = W.with_policies(wl, W.MLP_F32, [8 * actions, 512, 500, actions], bias_var=0.05)
+    pairs = W.random_pairs(3, 70, 2)
+    a = run_gpu(wl, trace=False, pairs=pairs)
+    _same(a, run_gpu(wl, snaps=[0, horizon - 1], pairs=pairs))
+    b = run_gpu(_policies(wl, 256), trace=False, pairs=pairs)
+    assert np.array_equal(a["returns"].view(np.uint32), b["returns"].view(np.uint32))
+    assert actions == 1 or np.unique(a["returns"]).size > 2
+
+
+@pytest.mark.parametrize("grid", [5, 6, 7, 16])
+@pytest.mark.parametrize("kind,dims", [(W.MLP_BF16, [75, 128, 128, 5]),
+                                       (W.MLP_F32, [75, 33, 20, 5])])
+def test_pursuit_grids_and_policies(kind, dims, grid):
+    wl = dataclasses.replace(W.make(3, P=4, n_envs=257, horizon=33), grid=grid)
+    wl = W.with_policies(wl, kind, dims, bias_var=0.05)
+    _check(wl, snaps=[0, 7, 32])
+
+
+@pytest.mark.parametrize("actions", [2, 5, 8, 9, 17, 32])
+@pytest.mark.parametrize("horizon", [1, 3, 40])
+def test_matrix_actions_and_horizons(actions, horizon):
+    rng = np.random.default_rng([1, actions])
+    wl = dataclasses.replace(
+        W.make(1, P=4, per_pair=9, horizon=horizon), n_actions=actions,
+        A=rng.uniform(-1, 1, (actions, actions)).astype(np.float32),
+        tab_logits=rng.standard_normal((4, actions)).astype(np.float32))
+    _check(wl)
+
+
+ROUTES = {
+    "iter_f32": lambda n: W.make(2, P=3, per_pair=1, horizon=5),
+    "iter_f32_generic": lambda n: W.with_policies(W.make(2, P=3, per_pair=1, horizon=5),
+                                                  W.MLP_F32, [24, 40, 30, 3], bias_var=0.05),
+    "iter_bf16": lambda n: W.with_policies(W.make(2, P=3, per_pair=1, horizon=5), W.MLP_BF16,
+                                           [24, 64, 64, 3], bias_var=0.05),
+    "pursuit_bf16": lambda n: W.with_policies(W.make(3, P=3, n_envs=n, horizon=5), W.MLP_BF16,
+                                              [75, 256, 256, 5], bias_var=0.05),
+    "pursuit_f32": lambda n: W.with_policies(W.make(3, P=3, n_envs=n, horizon=4), W.MLP_F32,
+                                             [75, 256, 256, 5], bias_var=0.05),
+}
+
+
+@pytest.mark.parametrize("n", [1, 65, 300])
+@pytest.mark.parametrize("name", list(ROUTES))
+def test_table_equals_step_by_step(name, n):
+    """A population of 3 takes the table; 256 policies of which a short batch
+    plays only 3 are evaluated step by step.  Both give the same returns."""
+    wl = dataclasses.replace(ROUTES[name](n), n_envs=n)
+    pairs = W.random_pairs(3, n, 2)
+    a = run_gpu(wl, trace=False, pairs=pairs)
+    big = _policies(wl, 256)
+    b = run_gpu(big, snaps=[0, wl.horizon - 1], pairs=pairs)
+    say(f"[finite] {name} n={n}")
+    assert np.array_equal(a["returns"].view(np.uint32), b["returns"].view(np.uint32))
+    assert np.array_equal(a["table"]["counts"], b["table"]["counts"][:3, :3])
+    check_parity(big, b)
+
+
+def test_nan_and_bad_ids_are_flagged_without_a_trace():
+    import paper_2106_07551_amd as M
+    for wl in (W.make(2, P=3, per_pair=40, horizon=6), W.make(3, P=3, n_envs=200, horizon=6)):
+        wl.weights = [w.copy() for w in wl.weights]
+        wl.weights[1][1, 2, 3] = np.float32("nan")
+        pairs = W.random_pairs(3, wl.n_envs, 2)
+        t = run_gpu(wl, trace=False, check=False, pairs=pairs)["table"]
+        assert t["status"] == M.binding.E_DEVICE and t["device_flags"] == 2
+        pairs[:] = 0                           # the NaN policy is in the table, unplayed
+        t = run_gpu(wl, trace=False, check=False, pairs=pairs)["table"]
+        assert t["status"] == M.binding.MALIB_OK
+        pairs[7, 1] = 3
+        t = run_gpu(wl, trace=False, check=False, pairs=pairs)["table"]
+        assert t["status"] == M.binding.E_DEVICE and t["device_flags"] == 1
+
+
+@pytest.mark.parametrize("warm,played", [(60, 5), (5, 60), (1, 60), (60, 1)])
+def test_capture_after_a_batch_of_another_horizon(warm, played):
+    """A batch outside the capture leaves room for one of the same size inside,
+    whichever of the two ways each of them takes."""
+    from paper_2106_07551_amd import workload_io as IO
+    wl = _policies(W.make(2, P=3, per_pair=1), 256)
+    n = 60
+    env = IO.make_env(wl)
+    pt = torch.from_numpy(W.random_pairs(256, n, 2)).cuda()
+    ref, ret = (torch.empty((2, n), dtype=torch.float32, device="cuda") for _ in range(2))
+    eager, pop = IO.make_population(wl), IO.make_population(wl)
+    eager.rollout(env, n, pt, wl.seed, played, returns=ref)
+    pop.rollout(env, n, pt, wl.seed, warm)
+    pop.payoff(reset=True)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        pop.rollout(env, n, pt, wl.seed, played, returns=ret)
+    for rep in range(3):
+        say(f"[finite] warm {warm} played {played} replay {rep}")
+        ret.fill_(float("nan"))
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(ret, ref)
+        pop.payoff(reset=True)
+    pop.close()
+    eager.close()
