@@ -80,3 +80,16 @@ def test_alpharank_on_a_4v4_table():
     ref = oracle.alpharank(game.cpu().numpy(), 1.0, 50)
     pop.close()
     assert _close(pi.cpu().numpy(), ref)
+
+
+# both sides of every register block size and of the workspace kernel, odd and
+# even (the pairs of policies are enumerated differently)
+@pytest.mark.parametrize("P", [4, 5, 32, 33, 64, 65, 96, 97, 160, 161, 224, 225])
+def test_alpharank_block_sizes(P):
+    import oracle
+    rng = np.random.default_rng(P)
+    M = rng.normal(size=(P, P))
+    M[0, 1] = M[1, 0]                                # a neutral pair
+    pi, sigma = _gpu_ar(M, 0.8, 50)
+    assert _close(pi, oracle.alpharank(M, 0.8, 50))
+    assert np.array_equal(sigma[0], pi.astype(np.float32))

@@ -92,3 +92,15 @@ def test_lp_non_finite_game_gives_nan(bad, P):
     assert np.isnan(x.cpu().numpy()).all() and np.isnan(y.cpu().numpy()).all()
     assert np.isnan(sigma.cpu().numpy()).all()
     assert int(piv.cpu()[0]) == -1
+
+
+# both sides of every register block size (16-wide blocks, then the 512-thread
+# grids) and of the workspace kernel
+@pytest.mark.parametrize("P", [16, 17, 33, 49, 64, 65, 80, 81, 112, 113, 129, 160, 161, 192, 193,
+                               224, 225])
+def test_lp_block_sizes(P):
+    rng = np.random.default_rng(77 + P)
+    M = rng.normal(size=(P, P))
+    _check(M, "normal")
+    if P <= 113:
+        _check(rng.integers(-1, 2, size=(P, P)).astype(np.float64), "integer ties")

@@ -298,3 +298,13 @@ def test_psro_convergence_on_device():
         assert imp <= float(gap.cpu()[0]) + 1e-12
         worst.append(imp)
     assert worst[-1] < worst[0] and worst[-1] < 0.02
+
+
+@pytest.mark.parametrize("P", [1, 3, 64, 65, 128, 129, 192, 256])
+def test_solve_fp_ties_in_the_high_words(P):
+    """Payoffs that differ in their lowest bits only, of either sign: sums that
+    share their high 32 bits are told apart by the low ones, equal ones by index."""
+    rng = np.random.default_rng(900 + P)
+    M = (1.0 + rng.integers(-3, 4, size=(P, P)) * 2.0 ** -46) * \
+        rng.choice([-1.0, 1.0, 1.0, 1.0], size=(P, 1))
+    _check_solve(M, 300)
