@@ -373,8 +373,9 @@ malib_status malib_expansion_pairs(int32_t n_policies, int32_t first_new, int32_
  * x is the first 32-bit lane of the Philox block (g, 0, 2<<32 | k, 0) and T_m
  * = floor(2^32 * C_m) from the fp64 cumulative sum C of the normalized row
  * (T_{P-1} = 2^32).  Policies with zero mass are never drawn.  The
- * thresholds are computed on the host and uploaded on `stream`, which is
- * synchronized once before the sampling kernel is enqueued.
+ * thresholds are computed on the host; up to 448 (n_sigma * n_policies) travel
+ * with the sampling kernel's arguments, more are uploaded on `stream`, which is
+ * then synchronized once before the kernel is enqueued.
  */
 malib_status malib_meta_sample(const float* sigma, int32_t n_sigma, int32_t n_policies,
                                int64_t n_envs, int32_t n_agents, uint64_t seed,
@@ -424,7 +425,7 @@ malib_status malib_solve_fp(const double* M, int32_t n_policies, int32_t iterati
  *  M:      device fp64 [P][P], finite (a NaN or infinite entry gives NaN
  *          value, x, y and sigma, and pivots = -1).
  *  work:   device fp64 [P+1][2P+1] workspace, needed for P > 96 (NULL
- *          allowed below: the tableau then lives in LDS).
+ *          allowed below: the tableau then lives in registers).
  *  value:  device fp64 [1]; x, y: device fp64 [P] (row and column side).
  *  sigma:  device fp32 [2][P] or NULL: x and y as weight rows for
  *          malib_meta_sample_device.
@@ -454,7 +455,7 @@ malib_status malib_solve_lp(const double* M, int32_t n_policies, double* work, d
  *  alpha:  ranking intensity, finite, >= 0 (0: the uniform distribution).
  *  m:      population size, 1 .. 10^6.
  *  work:   device fp64 [P][P] workspace, needed for P > 128 (NULL allowed
- *          below: the chain then lives in LDS).
+ *          below: the chain then lives in registers).
  *  pi:     device fp64 [P] output.
  *  sigma:  device fp32 [2][P] or NULL: pi in both weight rows, usable
  *          directly by malib_meta_sample_device.

@@ -982,6 +982,15 @@ static malib_status launch_rollout(malib_pop_t pop, const malib_env_desc* env, i
         fl.log = trace ? trace->actions : nullptr;
         fl.state = cur;
         fl.done = done;
+        // the returns where the caller wants them, if this device can write there
+        if (returns) {
+            hipPointerAttribute_t at;
+            if (hipPointerGetAttributes(&at, returns) == hipSuccess &&
+                at.type == hipMemoryTypeDevice && at.device == pop->device)
+                ret = returns;
+            else
+                (void)hipGetLastError();
+        }
         fl.ret = ret;
         fl.frames = pop->dev_frames;
         fl.flags = pop->dev_flags;
@@ -1084,7 +1093,7 @@ static malib_status launch_rollout(malib_pop_t pop, const malib_env_desc* env, i
         HIP_TRY(launch_payoff(ret, pair_assign, n_envs, n_agents, plan.team, pop->P, pop->sum,
                               pop->sumsq, pop->cnt, s));
     pend(pi);
-    if (returns)
+    if (returns && returns != ret)
         HIP_TRY(hipMemcpyAsync(returns, ret, sizeof(float) * ns, hipMemcpyDeviceToDevice, s));
     if (env->kind != MALIB_ENV_PURSUIT)
         pop->host_frames += ns * (int64_t)horizon;
@@ -1281,50 +1290,29 @@ malib_status malib_payoff_eval(malib_pop_t pop, void* stream, int32_t reset, dou
         return fail(MALIB_E_INVAL, "pop is NULL");
     hipStream_t s = (hipStream_t)stream;
     const size_t PP = (size_t)pop->P * pop->P;
-    // the whole accumulator block in one copy (stream-ordered after the
-    // batches), into the handle's pinned buffer
-    HIP_TRY(hipMemcpyAsync(pop->host_acc, pop->acc, sizeof(unsigned long long) * (3 * PP + 2),
-                           hipMemcpyDeviceToHost, s));
+    // one launch (stream-ordered after the batches) finalizes the table into the
+    // handle's pinned buffer and clears; complete before returning, so the next
+    // batch may run on any stream
+    HIP_TRY(launch_read_table(pop->acc, (int64_t)PP, reset ? 1 : 0, pop->host_acc, s));
     HIP_TRY(hipStreamSynchronize(s));
-    const long long* sum = reinterpret_cast<const long long*>(pop->host_acc);
-    const long long* sq = sum + PP;
-    const long long* cnt = sum + 2 * PP;
+    if (mean)
+        memcpy(mean, pop->host_acc, sizeof(double) * PP);
+    if (counts)
+        memcpy(counts, pop->host_acc + PP, sizeof(int64_t) * PP);
+    if (stderr_out)
+        memcpy(stderr_out, pop->host_acc + 2 * PP, sizeof(double) * PP);
     const unsigned long long frames = pop->host_acc[3 * PP];
     int flags;
     memcpy(&flags, pop->host_acc + 3 * PP + 1, sizeof(int));
-    for (size_t i = 0; i < PP; ++i) {
-        double n = (double)cnt[i];
-        double m = cnt[i] > 0 ? ldexp((double)sum[i], -32) / n : NAN;
-        if (mean)
-            mean[i] = m;
-        if (counts)
-            counts[i] = cnt[i];
-        if (stderr_out) {
-            if (cnt[i] < 2) {
-                stderr_out[i] = NAN;
-            } else {
-                double s2 = ldexp((double)sq[i], -20);
-                double var = (s2 - n * m * m) / (n - 1.0);
-                stderr_out[i] = sqrt(var > 0.0 ? var / n : 0.0);
-            }
-        }
-    }
     if (stats) {
         stats->live_frames = pop->host_frames + (int64_t)frames;
         stats->envs = pop->envs;
         stats->device_flags = flags;
     }
-    // clears are stream-ordered and complete before returning, so the next
-    // batch may run on any stream
     if (reset) {
-        HIP_TRY(hipMemsetAsync(pop->acc, 0, sizeof(unsigned long long) * (3 * PP + 1), s));
         pop->host_frames = 0;
         pop->envs = 0;
     }
-    if (flags)
-        HIP_TRY(hipMemsetAsync(pop->dev_flags, 0, sizeof(int), s));
-    if (reset || flags)
-        HIP_TRY(hipStreamSynchronize(s));
     if (flags)
         return fail(MALIB_E_DEVICE, "device flagged bad data (flags 0x%x:%s%s)", flags,
                     (flags & kErrPid) ? " policy id out of range" : "",
@@ -1376,6 +1364,11 @@ malib_status malib_meta_sample(const float* sigma, int32_t n_sigma, int32_t P, i
     if (n_envs == 0)
         return MALIB_OK;
     hipStream_t s = (hipStream_t)stream;
+    if ((int)thr.size() <= kMaxThresholdArgs) {
+        HIP_TRY(launch_meta_sample_args(thr.data(), (int)thr.size(), default_seat_map(n_sigma), P,
+                                        n_envs, n_agents, seed, env_offset, out, s));
+        return MALIB_OK;
+    }
     // Thresholds live in a device buffer that is freed in stream order; the
     // copy is staged synchronously from pageable memory before returning.
     unsigned long long* d_thr = nullptr;

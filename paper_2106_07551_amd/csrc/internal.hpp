@@ -66,7 +66,7 @@ struct Pop {
     unsigned long long* cnt = nullptr;
     unsigned long long* dev_frames = nullptr;
     int* dev_flags = nullptr;
-    unsigned long long* host_acc = nullptr;   // pinned copy of acc
+    unsigned long long* host_acc = nullptr;   // pinned: the finalized table (launch_read_table)
     int64_t host_frames = 0;   // frames of env families with no early termination
     int64_t envs = 0;
     // scratch, grown on demand
@@ -141,6 +141,14 @@ hipError_t launch_expansion_pairs(int P, int first, int per_pair, int n_agents, 
 hipError_t launch_meta_sample(const unsigned long long* thr, uint32_t seat_map, int P,
                               int64_t n_envs, int n_agents, uint64_t seed, int64_t env_offset,
                               int32_t* out, hipStream_t s);
+
+// The same from host thresholds, at most kMaxThresholdArgs of them (n_sigma P),
+// as kernel arguments.
+constexpr int kMaxThresholdArgs = 448;
+hipError_t launch_meta_sample_args(const unsigned long long* host_thr, int n_thr,
+                                   uint32_t seat_map, int P, int64_t n_envs, int n_agents,
+                                   uint64_t seed, int64_t env_offset, int32_t* out,
+                                   hipStream_t s);
 
 // Gumbel-max action sampling, done by the env-step kernels for the slots of
 // their envs (gumbel_action): the step's logits, the Philox key and counter
@@ -324,6 +332,12 @@ struct FiniteLaunch {
 };
 hipError_t launch_finite(const FiniteLaunch& L, hipStream_t s);
 hipError_t launch_finite_logits(const FiniteLaunch& L, float* out, hipStream_t s);
+
+// The table finalized into (pinned, device-visible) `out` [3 PP + 2]: mean,
+// count and standard error of each cell, the live-frame counter, the error flags
+// (cleared here); the sums, counts and frames cleared with `reset`.
+hipError_t launch_read_table(unsigned long long* acc, int64_t PP, int reset,
+                             unsigned long long* out, hipStream_t s);
 
 // Diagnostics.
 hipError_t launch_debug_bf16(const float* x, uint16_t* y, int64_t n, hipStream_t s);

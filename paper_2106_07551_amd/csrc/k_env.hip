@@ -1171,4 +1171,52 @@ hipError_t launch_payoff(const float* ret, const int32_t* pids, int64_t n_envs, 
     return hipGetLastError();
 }
 
+// ------------------------------------------------------------ table read-back
+
+// One thread per cell: mean = sum 2^-32 / n (NaN for an empty cell), standard
+// error sqrt(variance / n) with the variance from the sums (NaN below two
+// simulations).  Writes the finalized table to host memory and clears what the
+// caller asked for in the same launch, so a read-back is one launch and one
+// synchronization.
+__global__ void read_table_kernel(unsigned long long* __restrict__ acc, int64_t PP, int reset,
+                                  unsigned long long* __restrict__ out)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < PP) {
+        const long long cnt = (long long)acc[2 * PP + i];
+        double mean = (double)NAN, err = (double)NAN;
+        if (cnt > 0) {
+            const double n = (double)cnt;
+            mean = (double)(long long)acc[i] * 0x1p-32 / n;
+            if (cnt >= 2) {
+                const double s2 = (double)(long long)acc[PP + i] * 0x1p-20;
+                const double var = (s2 - n * mean * mean) / (n - 1.0);
+                err = sqrt(var > 0.0 ? var / n : 0.0);
+            }
+        }
+        out[i] = (unsigned long long)__double_as_longlong(mean);
+        out[PP + i] = (unsigned long long)cnt;
+        out[2 * PP + i] = (unsigned long long)__double_as_longlong(err);
+        if (reset) {
+            acc[i] = 0;
+            acc[PP + i] = 0;
+            acc[2 * PP + i] = 0;
+        }
+    } else if (i == PP) {
+        out[3 * PP] = acc[3 * PP];
+        if (reset)
+            acc[3 * PP] = 0;
+    } else if (i == PP + 1) {
+        out[3 * PP + 1] = acc[3 * PP + 1];
+        acc[3 * PP + 1] = 0;
+    }
+}
+
+hipError_t launch_read_table(unsigned long long* acc, int64_t PP, int reset,
+                             unsigned long long* out, hipStream_t s)
+{
+    read_table_kernel<<<(int)((PP + 2 + 255) / 256), 256, 0, s>>>(acc, PP, reset, out);
+    return hipGetLastError();
+}
+
 }  // namespace malib

@@ -36,6 +36,57 @@ __global__ void meta_sample_kernel(const unsigned long long* __restrict__ thr, u
     out[i] = lo;
 }
 
+// The same draws with the thresholds in the kernel's arguments (from the host,
+// few enough), staged in LDS for the search: no buffer, copy or synchronization.
+struct ThresholdArgs {
+    unsigned long long t[kMaxThresholdArgs];
+};
+
+__global__ __launch_bounds__(256) void meta_sample_args_kernel(ThresholdArgs thr, int n_thr,
+                                                               uint32_t seat_map, int P,
+                                                               int64_t n_envs, int n_agents,
+                                                               uint64_t seed, int64_t env_offset,
+                                                               int32_t* __restrict__ out)
+{
+    __shared__ unsigned long long T_s[kMaxThresholdArgs];
+    for (int k = threadIdx.x; k < n_thr; k += 256)
+        T_s[k] = thr.t[k];
+    __syncthreads();
+    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n_envs * n_agents)
+        return;
+    int64_t e = i / n_agents;
+    int seat = (int)(i - e * n_agents);
+    u64x4 blk = stream_block(seed, (uint64_t)(env_offset + e), 0, kPurposeMeta, seat, 0);
+    unsigned long long x = (uint32_t)blk.x;
+    const unsigned long long* T = T_s + ((seat_map >> (4 * seat)) & 0xFu) * P;
+    int lo = 0, hi = P - 1;
+    while (lo < hi) {
+        int mid = (lo + hi) >> 1;
+        if (x < T[mid])
+            hi = mid;
+        else
+            lo = mid + 1;
+    }
+    out[i] = lo;
+}
+
+hipError_t launch_meta_sample_args(const unsigned long long* host_thr, int n_thr,
+                                   uint32_t seat_map, int P, int64_t n_envs, int n_agents,
+                                   uint64_t seed, int64_t env_offset, int32_t* out,
+                                   hipStream_t s)
+{
+    if (n_thr > kMaxThresholdArgs)
+        return hipErrorInvalidValue;
+    ThresholdArgs thr;
+    std::copy(host_thr, host_thr + n_thr, thr.t);
+    std::fill(thr.t + n_thr, thr.t + kMaxThresholdArgs, 0ull);
+    const int64_t total = n_envs * n_agents;
+    meta_sample_args_kernel<<<(int)((total + 255) / 256), 256, 0, s>>>(
+        thr, n_thr, seat_map, P, n_envs, n_agents, seed, env_offset, out);
+    return hipGetLastError();
+}
+
 hipError_t launch_meta_sample(const unsigned long long* thr, uint32_t seat_map, int P,
                               int64_t n_envs, int n_agents, uint64_t seed, int64_t env_offset,
                               int32_t* out, hipStream_t s)

@@ -179,3 +179,35 @@ def test_capture_after_a_batch_of_another_horizon(warm, played):
         pop.payoff(reset=True)
     pop.close()
     eager.close()
+
+
+@pytest.mark.parametrize("seats,P", [(8, 56), (8, 57), (2, 224), (2, 225), (1, 256)])
+def test_meta_sample_thresholds_in_arguments_or_memory(seats, P):
+    """448 thresholds travel with the kernel's arguments, more do not."""
+    import oracle
+    import paper_2106_07551_amd as M
+    s = np.random.default_rng(P).random((seats, P)).astype(np.float32)
+    s[0, : P // 2] = 0
+    g = M.meta_sample(s, P, 700, seats, 91, env_offset=5).cpu().numpy()
+    assert np.array_equal(g, oracle.meta_sample(s, P, 700, seats, 91, 5))
+
+
+def test_returns_buffer_and_table_read_back():
+    """Returns written into the caller's buffer or kept by the handle: the same
+    table; reading it without reset leaves it, with reset empties it."""
+    from paper_2106_07551_amd import workload_io as IO
+    wl = W.make(3, P=4, n_envs=500, horizon=12)
+    env, pop = IO.make_env(wl), IO.make_population(wl)
+    pt = torch.from_numpy(W.random_pairs(4, 500, 2)).cuda()
+    ret = torch.full((2, 500), float("nan"), device="cuda")
+    pop.rollout(env, 500, pt, wl.seed, 12, returns=ret)
+    a, b = pop.payoff(), pop.payoff(reset=True)
+    assert (pop.payoff()["counts"] == 0).all() and np.isnan(pop.payoff()["mean"]).all()
+    pop.rollout(env, 500, pt, wl.seed, 12)
+    c = pop.payoff(reset=True)
+    for t in (b, c):
+        for k in ("mean", "counts", "stderr"):
+            assert a[k].tobytes() == t[k].tobytes()
+        assert (a["live_frames"], a["envs"]) == (t["live_frames"], t["envs"])
+    assert torch.isfinite(ret).all()
+    pop.close()
