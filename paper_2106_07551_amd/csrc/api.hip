@@ -785,10 +785,9 @@ static void buffer_sizes(const Pop& pop, const malib_env_desc* env, int64_t n_en
     sz[14] = plan.kernel_sample ? (size_t)ns : 0;                        // actions
 }
 
-// The same for a finite plan without trace: the returns, the table with its
-// virtual batch, and what the payoff reduction of large populations needs.
-static void finite_buffer_sizes(const Pop& pop, int64_t n_envs, const RolloutPlan& plan,
-                                size_t (&sz)[kNumBufs])
+// The same for a finite plan without trace: the returns and the table with its
+// virtual batch.
+static void finite_buffer_sizes(const Pop& pop, const RolloutPlan& plan, size_t (&sz)[kNumBufs])
 {
     const int64_t ns = plan.ns, tenvs = (int64_t)pop.P * plan.rows, tns = tenvs * plan.row_seats;
     for (size_t& x : sz)
@@ -796,18 +795,11 @@ static void finite_buffer_sizes(const Pop& pop, int64_t n_envs, const RolloutPla
     sz[1] = sizeof(float) * ns;                                          // ret
     if (!plan.mlp)
         return;
-    const bool bucket = !payoff_stream_fits(pop.P);
-    const size_t pc = bucket ? (size_t)pop.P * plan.n_chunks : 0;
     sz[0] = sizeof(float) * tns * pop.A;                                 // logits: the table
     sz[3] = 2 * (size_t)tenvs;                                           // state1: its envs
-    sz[7] = sizeof(int32_t) * std::max(tns, bucket ? ns : 0);            // perm
-    sz[8] = sz[7];                                                       // perm_env
-    sz[9] = sizeof(int32_t) * pc;                                        // hist
-    sz[10] = sizeof(int32_t) * pc;                                       // base
-    sz[11] = sizeof(int32_t) * (pop.P + 1);                              // offsets
-    sz[12] = sizeof(int32_t) * (pop.P + 1);                              // tile_off
-    sz[13] = sizeof(int4) * (size_t)std::max(plan.t_entries, bucket ? plan.max_tiles : 0);
-    (void)n_envs;
+    sz[7] = sizeof(int32_t) * tns;                                       // perm
+    sz[8] = sizeof(int32_t) * tns;                                       // perm_env
+    sz[13] = sizeof(int4) * (size_t)plan.t_entries;                      // tile_info
 }
 
 // What the handle keeps for a batch: room for both ways of playing it, so that
@@ -818,7 +810,7 @@ static void handle_sizes(const Pop& pop, const malib_env_desc* env, int64_t n_en
     buffer_sizes(pop, env, n_envs, plan, sz);
     if (plan.finite) {
         size_t fz[kNumBufs];
-        finite_buffer_sizes(pop, n_envs, plan, fz);
+        finite_buffer_sizes(pop, plan, fz);
         for (int i = 0; i < kNumBufs; ++i)
             sz[i] = std::max(sz[i], fz[i]);
     }
@@ -942,6 +934,7 @@ static malib_status launch_rollout(malib_pop_t pop, const malib_env_desc* env, i
                    : hipMemcpyAsync(dst, cur, snap_b, hipMemcpyDeviceToDevice, s);
     };
     int pi;
+    const bool added = plan.finite && finite_adds(n_envs, pop->P);
     if (plan.finite) {
         // ---- few distinct observations: the table, then the whole horizon
         const bool traced = trace && (snap_of || trace->perm || trace->offsets);
@@ -1007,11 +1000,16 @@ static malib_status launch_rollout(malib_pop_t pop, const malib_env_desc* env, i
             }
             fl.t1 = t;
             fl.keep = traced;
+            if (t == horizon && added) {
+                fl.sum = pop->sum;
+                fl.sumsq = pop->sumsq;
+                fl.cnt = pop->cnt;
+            }
             pi = pbeg(MALIB_K_ENV);
             HIP_TRY(launch_finite(fl, s));
             pend(pi);
         }
-        if (mlp && (!payoff_stream_fits(pop->P) || traced)) {
+        if (mlp && traced) {
             pi = pbeg(MALIB_K_SETUP);
             HIP_TRY(bucket());
             pend(pi);
@@ -1081,7 +1079,9 @@ static malib_status launch_rollout(malib_pop_t pop, const malib_env_desc* env, i
 
     // ---- payoff reduction
     pi = pbeg(MALIB_K_PAYOFF);
-    if (payoff_stream_fits(pop->P))
+    if (added)
+        ;   // the envs have added themselves
+    else if (payoff_stream_fits(pop->P))
         HIP_TRY(launch_payoff_stream(ret, pair_assign, n_envs, n_agents, ea.team_row,
                                      ea.team_col, pop->P, pop->n_cus, pop->sum, pop->sumsq,
                                      pop->cnt, s));
@@ -1262,7 +1262,7 @@ malib_status malib_rollout_batch_noalloc(malib_pop_t pop, const malib_env_desc* 
     };
     bool fits = false;
     if (plan.finite) {
-        finite_buffer_sizes(*pop, n_envs, plan, sz);
+        finite_buffer_sizes(*pop, plan, sz);
         fits = carve();
     }
     if (!fits) {   // step by step

@@ -329,7 +329,20 @@ struct FiniteLaunch {
     float* ret;
     unsigned long long* frames;
     int* flags;
+    // the table's accumulators, for the launch that plays the last step of a
+    // batch with finite_adds; null otherwise
+    unsigned long long *sum, *sumsq, *cnt;
 };
+// Whether a batch's envs add to the table by themselves (one set of atomics per
+// env, or per wavefront of one pair): where the payoff kernels would need the
+// slots sorted by policy (P > 64), and where few envs share a cell (pursuit, 10
+// steps: P = 100, 16384 envs 106 -> 68 us a fill, 131072 envs 129 -> 89; P = 64,
+// 16384 envs 67 -> 63, 65536 envs 69 -> 74; P = 32, 8192 envs 57 -> 55, 32768
+// envs 56 -> 63 us).
+inline bool finite_adds(int64_t n_envs, int P)
+{
+    return P * P > kPayoffStreamMaxCells || n_envs <= 8 * (int64_t)P * P;
+}
 hipError_t launch_finite(const FiniteLaunch& L, hipStream_t s);
 hipError_t launch_finite_logits(const FiniteLaunch& L, float* out, hipStream_t s);
 

@@ -153,6 +153,12 @@ struct FiniteArgs {
     float* ret;              // [2][n]
     unsigned long long* frames;
     int* flags;
+    // payoff table accumulators [P][P] (null: reduced by another kernel): the
+    // row side is seat row_seat
+    unsigned long long* sum;
+    unsigned long long* sumsq;
+    unsigned long long* cnt;
+    int row_seat;
 };
 
 // The two seats' actions exchanged between neighbouring lanes.
@@ -220,12 +226,11 @@ __global__ __launch_bounds__(256) void finite_kernel(FiniteArgs f)
     const bool valid = e < f.n, writer = valid && li < 2;
     const int64_t ec = valid ? e : 0;
     const uint64_t g = (uint64_t)(f.env_offset + ec);
-    int p = f.pids[2 * ec + seat];
-    if (p < 0 || p >= f.P) {
-        if (writer)
-            atomicOr(f.flags, kErrPid);
-        p = 0;
-    }
+    const int pid = f.pids[2 * ec + seat];
+    const bool known = pid >= 0 && pid < f.P;
+    if (!known && writer)
+        atomicOr(f.flags, kErrPid);
+    const int p = known ? pid : 0;
     // this lane's rows of the table
     int stride = f.per_seat ? 2 * A : A;
     const float* tab = f.table + (int64_t)p * f.rows * stride + (f.per_seat ? seat * A : 0);
@@ -439,6 +444,37 @@ __global__ __launch_bounds__(256) void finite_kernel(FiniteArgs f)
             }
         }
     }
+    if (f.sum) {
+        // the env's entry of the table, by its row seat's lane (neither seat's id
+        // out of range): one set of atomics per wavefront where all its envs play
+        // one pair, else per env
+        const int other = swap_pair(known ? pid : -1);
+        const bool adds = writer && seat == f.row_seat && known && other >= 0;
+        const int cell = adds ? pid * f.P + other : -1;
+        const double gd = (double)ret;
+        long long fx = adds ? __double2ll_rn(gd * 4294967296.0) : 0;
+        long long fsq = adds ? __double2ll_rn(gd * gd * 1048576.0) : 0;
+        const unsigned long long who = __ballot(adds);
+        if (who) {
+            const int c0 = __shfl(cell, __ffsll(who) - 1, 64);
+            if (__ballot(adds && cell != c0) == 0ull) {
+#pragma unroll
+                for (int o = 32; o > 0; o >>= 1) {
+                    fx += __shfl_xor(fx, o, 64);
+                    fsq += __shfl_xor(fsq, o, 64);
+                }
+                if ((threadIdx.x & 63) == 0) {
+                    atomicAdd(&f.sum[c0], (unsigned long long)fx);
+                    atomicAdd(&f.sumsq[c0], (unsigned long long)fsq);
+                    atomicAdd(&f.cnt[c0], (unsigned long long)__popcll(who));
+                }
+            } else if (adds) {
+                atomicAdd(&f.sum[cell], (unsigned long long)fx);
+                atomicAdd(&f.sumsq[cell], (unsigned long long)fsq);
+                atomicAdd(&f.cnt[cell], 1ull);
+            }
+        }
+    }
     if constexpr (PURSUIT) {
         // live agent-frames, two per env and step
         int mine = writer ? lives : 0;
@@ -481,6 +517,10 @@ hipError_t launch_finite(const FiniteLaunch& L, hipStream_t s)
     f.ret = L.ret;
     f.frames = L.frames;
     f.flags = L.flags;
+    f.sum = L.sum;
+    f.sumsq = L.sumsq;
+    f.cnt = L.cnt;
+    f.row_seat = (e.team_row & 1u) ? 0 : 1;
     const int64_t n = L.n_envs;
     const int H = L.t1 - L.t0;
     // lanes per env: the noise of more steps at once where the batch leaves the

@@ -211,3 +211,24 @@ def test_returns_buffer_and_table_read_back():
         assert (a["live_frames"], a["envs"]) == (t["live_frames"], t["envs"])
     assert torch.isfinite(ret).all()
     pop.close()
+
+
+@pytest.mark.parametrize("P,n", [(5, 199), (5, 200), (5, 201), (70, 300), (256, 5000)])
+@pytest.mark.parametrize("swap", [False, True])
+def test_envs_add_to_the_table(P, n, swap):
+    """Both sides of the rule (8 envs per cell, P > 64), either seat on the row
+    side, a blocked wavefront, and an id out of range, which adds nothing."""
+    import oracle
+    import paper_2106_07551_amd as M
+    wl = W.with_policies(W.make(3, P=P, n_envs=n, horizon=9), W.MLP_BF16, [75, 64, 64, 5])
+    wl.team = np.array([-1, 1] if swap else [1, -1], np.int8)
+    pairs = W.random_pairs(P, n, 2)
+    pairs[64:128] = [3, 1]
+    g = run_gpu(wl, trace=False, pairs=pairs)
+    mean, cnt, _, _ = oracle.payoff(g["returns"], pairs, wl.team, P)
+    assert np.array_equal(g["table"]["counts"], cnt)
+    assert np.abs(g["table"]["mean"] - mean)[cnt > 0].max() <= 1e-9
+    pairs[10, 1] = P
+    bad = run_gpu(wl, trace=False, check=False, pairs=pairs)["table"]
+    assert bad["status"] == M.binding.E_DEVICE and bad["device_flags"] == 1
+    assert bad["counts"].sum() == n - 1
