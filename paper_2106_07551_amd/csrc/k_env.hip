@@ -744,25 +744,39 @@ hipError_t launch_env_step(const EnvArgs& e, const SampleArgs& sa, int64_t n_env
             return hipErrorInvalidValue;
         const FeatArgs f{e.WP, e.emb, e.u, e, sa, n_envs, (const float*)state_in,
                          (float*)state_out, ret};
-        // 16-env tiles up to one per CU, 32-env tiles (half the W traffic per
-        // env) beyond that: at d = 256, 4096 envs take 13 us with 16-env tiles,
-        // 6000 envs 19.2 us with 32-env and 22.6 us with 16-env tiles
+        // 32-env tiles read half as much of W per env, 16-env ones spread a
+        // batch better: up to one per CU (n <= 16 cus), and again where some CUs
+        // would get two 32-env tiles and others one (32 cus < n <= 48 cus).  us
+        // a step with 32- and with 16-env tiles, 256 CUs: d = 64 7.2 / 5.8 (5003
+        // envs), 8.7 / 7.7 (16384), 10.3 / 10.6 (20480); d = 128 9.2 / 9.0
+        // (5003), 13.1 / 12.3 (10000), 13.8 / 14.6 (13000); d = 256 19.9 / 19.0
+        // (5003), 30.8 / 27.5 (10000), 32.0 / 34.6 (13000); d = 512 45.9 / 45.3
+        // (5003), 49.7 / 51.3 (8192), 79.0 / 70.6 (10000), 81 / 88 (13000).
+        // One 16-env tile per CU takes more wavefronts (257 envs of 8 seats at
+        // d = 256: 12.8 us with 8, 12.2 with 16).
         const int64_t cus = e.n_cus > 0 ? e.n_cus : 256;
-        const bool small = n_envs <= 16 * cus;
-        if (e.d == 64 && small)
+        const bool one = n_envs <= 16 * cus, two = n_envs <= 32 * cus;
+        const bool three = n_envs <= 48 * cus, four = n_envs <= 64 * cus;
+        if (e.d == 64 && four)
             launch_feature<64, 1, 4, 4>(f, s);
         else if (e.d == 64)
             launch_feature<64, 2, 4, 4>(f, s);
-        else if (e.d == 128 && small)
+        else if (e.d == 128 && two)
             launch_feature<128, 1, 8, 8>(f, s);
+        else if (e.d == 128 && three)
+            launch_feature<128, 1, 4, 4>(f, s);
         else if (e.d == 128)
             launch_feature<128, 2, 8, 4>(f, s);
-        else if (e.d == 256 && small)
+        else if (e.d == 256 && one)
             launch_feature<256, 1, 16, 8>(f, s);
+        else if (e.d == 256 && three)
+            launch_feature<256, 1, 8, 4>(f, s);
         else if (e.d == 256)
             launch_feature<256, 2, 8, 2>(f, s);
-        else if (e.d == 512 && small)
+        else if (e.d == 512 && one)
             launch_feature<512, 1, 16, 4>(f, s);
+        else if (e.d == 512 && three && !two)
+            launch_feature<512, 1, 8, 4>(f, s);
         else if (e.d == 512)
             launch_feature<512, 2, 8, 2>(f, s);
         else

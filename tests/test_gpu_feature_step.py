@@ -1,7 +1,7 @@
 """The feature dynamics' step kernel at the sizes where its tiling can go
-wrong: one env, one less and one more than a 16- or 32-env tile, the last
-batch of 16-env tiles (16 per CU) and the first of 32-env tiles, for every
-state width; given and kernel-sampled actions, 2 to 8 seats.  States, returns
+wrong: one env, one less and one more than a 16- or 32-env tile, and both
+sides of the batch sizes (16, 32, 48 and 64 envs per CU) where the tile or the
+number of wavefronts changes, for every state width; given and kernel-sampled actions, 2 to 8 seats.  States, returns
 and rewards are compared bit for bit with the oracle's sequential fused chain
 (gpu_helpers.check_parity), also where products, sums and states are subnormal."""
 import numpy as np
@@ -31,7 +31,8 @@ def _edges(n, rng):
 @pytest.mark.parametrize("d", [64, 128, 256, 512])
 def test_step_tile_edges(d, sampled):
     cus = torch.cuda.get_device_properties(0).multi_processor_count
-    for k, n in enumerate([1, 15, 16, 17, 33, 16 * cus, 16 * cus + 1, 32 * cus + 31]):
+    for k, n in enumerate([1, 15, 16, 17, 33, 16 * cus, 16 * cus + 1, 32 * cus + 31,
+                           48 * cus + 1, 48 * cus, 64 * cus, 64 * cus + 1]):
         seats = [2, 8, 3, 5][k % 4]
         # fp32 policies leave the sampling to the step kernel
         wl = W.team_variant(seats, d=d, P=3, n_envs=n, horizon=2)
