@@ -55,9 +55,6 @@ def describe(wl):
     return d
 
 
-PEAK_F32_ALU_TFLOPS = 78.6   # fp32 FMA without packed fp32 (256 CU x 4 SIMD x 16 lanes x 2 x 2.4 GHz)
-
-
 def algorithmic_work(wl):
     """Per-launch algorithmic HBM bytes (and flops where the kernel is ALU- or
     MFMA-bound) of the per-step kernels: unique data each launch must read or
@@ -410,9 +407,9 @@ SWEEP_BASE = {"matrix": ("per_pair", 1024), "iter": ("per_pair", 4096),
 
 
 def bandwidth_sweep(factors, horizon):
-    """Bandwidth sweep of the streaming kernels: the env step (K2; the
-    4v4 game's K3, which is fp32-ALU-bound, for comparison) and the payoff
-    reduction (K4), with the env count of each workload scaled by each factor
+    """Bandwidth sweep of the streaming kernels: the env step (K2; the 4v4
+    game's K3, which is bound by the fp32 matrix cores, for comparison) and
+    the payoff reduction (K4), with the env count of each workload scaled by each factor
     and every launch timed with HIP events.  One JSON line per point, labelled
     "bandwidth_sweep"; not the bench metric."""
     import torch
@@ -455,7 +452,7 @@ def bandwidth_sweep(factors, horizon):
                 if kname == "env" and "flops" in work["env"]:
                     tf = work["env"]["flops"] / (avg_us * 1e-6) / 1e12
                     row["fp32_TFLOPs"] = round(tf, 2)
-                    row["alu_frac"] = round(tf / PEAK_F32_ALU_TFLOPS, 4)
+                    row["mfma_f32_frac"] = round(tf / PEAK_F32_MFMA_TFLOPS, 4)
                 print(json.dumps(row), flush=True)
             pop.close()
             del pairs
@@ -589,7 +586,8 @@ def main():
             kern[name]["hbm_frac"] = round(w["bytes"] / t / 1e9 / PEAK_HBM_GBS, 4)
             if name == "env" and "flops" in w:
                 kern[name]["fp32_TFLOPs"] = round(w["flops"] / t / 1e12, 2)
-                kern[name]["alu_frac"] = round(w["flops"] / t / 1e12 / PEAK_F32_ALU_TFLOPS, 4)
+                kern[name]["mfma_f32_frac"] = round(w["flops"] / t / 1e12 /
+                                                   PEAK_F32_MFMA_TFLOPS, 4)
     pop.profile_enable(False)
     traj = meta = expand = graph = None
     if not args.fill_only:

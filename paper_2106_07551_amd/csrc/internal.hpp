@@ -100,7 +100,7 @@ inline int max_tiles_for(int64_t n_slots, int P, int tile_rows)
 {
     return (int)((n_slots + tile_rows - 1) / tile_rows + P);
 }
-// Entries of the striped table of the 64-row bf16 kernel: max_tiles_for
+// Entries of the striped table (64-row bf16 and generic kernels): max_tiles_for
 // rounded up to the 8 XCD segments (one workgroup per entry).
 inline int striped_entries(int64_t n_slots, int P, int tile_rows)
 {

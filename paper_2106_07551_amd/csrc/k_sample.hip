@@ -1,5 +1,5 @@
 // Meta-strategy draws (policy id per env seat) on the Philox4x64-10 stream.
-// (Gumbel-max action sampling runs inside the env-step kernels: gumbel_action.)
+// (Gumbel-max action sampling runs inside the env-step, horizon and policy kernels.)
 #include "device.hpp"
 #include "internal.hpp"
 
