@@ -1054,9 +1054,10 @@ __global__ __launch_bounds__(bf16_tile_threads(HID), bf16_tile_waves_per_simd(HI
 // until every wavefront has read its inputs, then replace them in LDS.
 //
 // Bound: fp32 MFMA (157 TFLOP/s; the same SIMD cycles as the VALU), and at small
-// batches one tile's latency.  bf16 256-1024-1024-18, 9600 rows of 12 policies in
-// equal buckets: 210 us (122 TFLOP/s); fp32 128-256-256-18, 16000 rows: 39 us.
-// (One thread per unit with 8-row tiles took 3970 and 765 us.)
+// batches one tile's latency.  bf16 256-1024-1024-18, 5760 rows of 12 policies in
+// equal buckets: 201 us (76 TFLOP/s; 360 tiles leave 152 of 256 CUs with one, the
+// others with two take 148 us for their chains); fp32 128-256-256-18, 16000 rows:
+// 39 us.  (One thread per unit with 8-row tiles took 3970 and 765 us.)
 
 constexpr int kGenericThreads = 512;
 
