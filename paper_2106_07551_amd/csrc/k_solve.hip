@@ -38,6 +38,8 @@ constexpr int kDppQuadSwap1 = 0xB1;   // quad_perm [1, 0, 3, 2]
 constexpr int kDppQuadSwap2 = 0x4E;   // quad_perm [2, 3, 0, 1]
 constexpr int kDppHalfMirror = 0x141;
 constexpr int kDppRowMirror = 0x140;
+constexpr int kDppRowBcast15 = 0x142;   // lane 15 of each row to the next row
+constexpr int kDppRowBcast31 = 0x143;   // lane 31 to the rows above it
 
 // A reduction step's other value (every lane has a source in these patterns, so
 // the move folds into the instruction that uses it).
@@ -161,6 +163,56 @@ __device__ __forceinline__ void sort_key(double v, int& hi, unsigned int& lo)
     lo = (unsigned int)b ^ (unsigned int)s;
 }
 
+// The same across rows: lanes of the rows in ROWS take the pattern's source,
+// the others keep their own value.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_f64_rows(double x)
+{
+    const long long b = __double_as_longlong(x);
+    const int lo = __builtin_amdgcn_update_dpp((int)b, (int)b, CTRL, ROWS, 0xF, false);
+    const int hi =
+        __builtin_amdgcn_update_dpp((int)(b >> 32), (int)(b >> 32), CTRL, ROWS, 0xF, false);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+// The largest of x and the smallest of y over the wavefront, the same in
+// every lane; the two reductions interleave.  IEEE maxNum / minNum (one
+// v_max_f64 / v_min_f64 each): a NaN never replaces a number, and which of
+// +0 and -0 survives does not matter (the callers compare with ==, and take
+// the winning policy's own sum afterwards).
+__device__ __forceinline__ void wave_max_min(double& x, double& y)
+{
+    auto hi = [](double a, double b) { return __builtin_fmax(a, b); };
+    auto lo = [](double a, double b) { return __builtin_fmin(a, b); };
+    double dx = dpp_f64<kDppQuadSwap1>(x), dy = dpp_f64<kDppQuadSwap1>(y);
+    x = hi(x, dx);
+    y = lo(y, dy);
+    dx = dpp_f64<kDppQuadSwap2>(x);
+    dy = dpp_f64<kDppQuadSwap2>(y);
+    x = hi(x, dx);
+    y = lo(y, dy);
+    dx = dpp_f64<kDppHalfMirror>(x);
+    dy = dpp_f64<kDppHalfMirror>(y);
+    x = hi(x, dx);
+    y = lo(y, dy);
+    dx = dpp_f64<kDppRowMirror>(x);
+    dy = dpp_f64<kDppRowMirror>(y);
+    x = hi(x, dx);
+    y = lo(y, dy);
+    // rows: lane 15 of rows 0 and 2 into rows 1 and 3, then lane 31 into
+    // rows 2 and 3; lane 63 then holds the wavefront's result
+    dx = dpp_f64_rows<kDppRowBcast15, 0xA>(x);
+    dy = dpp_f64_rows<kDppRowBcast15, 0xA>(y);
+    x = hi(x, dx);
+    y = lo(y, dy);
+    dx = dpp_f64_rows<kDppRowBcast31, 0xC>(x);
+    dy = dpp_f64_rows<kDppRowBcast31, 0xC>(y);
+    x = hi(x, dx);
+    y = lo(y, dy);
+    x = readlane_f64(x, 63);
+    y = readlane_f64(y, 63);
+}
+
 // Simultaneous fictitious play on the zero-sum game with row payoff M
 // (P x P, fp64; meant for finite entries, a NaN anywhere in v or w leaves the
 // counts unspecified and sets gap to NaN): at iteration t, i_t = first argmax
@@ -173,8 +225,8 @@ __device__ __forceinline__ void sort_key(double v, int& hi, unsigned int& lo)
 // lowest lane (a ballot).  Bound by that chain's latency: the reduction runs on
 // the order-preserving high words, whose DPP steps are one instruction each, and
 // on the low words only where several policies share the extreme (1000
-// iterations at P = 128: 302 us with fp64 reductions, 263 us; P <= 64: 203 and
-// 160 us).  Writes sigma[0][k], sigma[1][k] = the play counts (weights for
+// iterations at P = 128: 302 us with fp64 reductions throughout, 269 us; P = 64:
+// 208 and 199 us).  Writes sigma[0][k], sigma[1][k] = the play counts (weights for
 // meta-sampling) and gap = (v[i] - w[j]) / T at the best responses i, j to the
 // final sums.
 template <int K, bool IN_LDS>
@@ -262,11 +314,22 @@ __global__ __launch_bounds__(64) void solve_fp_kernel(const double* __restrict__
             i = m[q] ? 64 * q + __ffsll(m[q]) - 1 : i;
         return min(i, P - 1);
     };
-    for (int t = 0; t < T; ++t) {
-        extremes();
-        if (__builtin_expect(tied(), 0))
-            low_words();
-        const int i = first(bi), j = first(bj);
+    // The same masks by fp64 maxima: no second pass, whatever is tied.
+    auto extremes_f64 = [&]() {
+        double lv = v[0], lw = w[0];
+#pragma unroll
+        for (int q = 1; q < K; ++q) {
+            lv = __builtin_fmax(lv, v[q]);
+            lw = __builtin_fmin(lw, w[q]);
+        }
+        wave_max_min(lv, lw);
+#pragma unroll
+        for (int q = 0; q < K; ++q) {
+            bi[q] = __ballot(v[q] == lv);
+            bj[q] = __ballot(w[q] == lw);
+        }
+    };
+    auto play = [&](int i, int j) {
         // every slot reads (a slot past P reads policy P - 1 and is never
         // looked at), so all loads issue before the first add waits
         double gv[K], gw[K];
@@ -284,6 +347,24 @@ __global__ __launch_bounds__(64) void solve_fp_kernel(const double* __restrict__
             v[q] = v[q] + gv[q];
             w[q] = w[q] + gw[q];
         }
+    };
+    // A game whose extremes tie in more than an eighth of the iterations (equal
+    // rows of policies without a played cell, duplicates) goes on with the fp64
+    // maxima.  us per 1000 iterations, tied throughout: 428 at P = 128 with the
+    // high words, 296 like this; 292 and 214 at P = 64.
+    int t = 0, ties = 0;
+    for (; t < T; ++t) {
+        extremes();
+        if (__builtin_expect(tied(), 0)) {
+            if (8 * ++ties > t + 64)
+                break;   // this iteration is played below
+            low_words();
+        }
+        play(first(bi), first(bj));
+    }
+    for (; t < T; ++t) {
+        extremes_f64();
+        play(first(bi), first(bj));
     }
 #pragma unroll
     for (int q = 0; q < K; ++q) {

@@ -308,3 +308,19 @@ def test_solve_fp_ties_in_the_high_words(P):
     M = (1.0 + rng.integers(-3, 4, size=(P, P)) * 2.0 ** -46) * \
         rng.choice([-1.0, 1.0, 1.0, 1.0], size=(P, 1))
     _check_solve(M, 300)
+
+
+@pytest.mark.parametrize("P", [2, 64, 66, 130, 256])
+def test_solve_fp_ties_of_unplayed_policies(P):
+    """Empty cells count 0: policies that never played share equal zero rows and
+    columns, which tie exactly (the first wins), also beside a policy whose sum
+    differs from theirs in the low bits only."""
+    rng = np.random.default_rng(950 + P)
+    for unplayed in (1, min(5, P - 1), P):
+        M = rng.standard_normal((P, P))
+        idle = rng.choice(P, size=unplayed, replace=False)
+        M[idle] = 0.0
+        M[:, idle] = 0.0
+        _check_solve(M, 200)
+        # all payoffs beside one value, a few of them off by its last bits
+        _check_solve(np.where(rng.random((P, P)) < 0.02, 2.0 ** -50, 0.0) + 0.5, 200)
