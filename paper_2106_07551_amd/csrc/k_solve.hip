@@ -352,8 +352,10 @@ __global__ __launch_bounds__(64) void solve_fp_kernel(const double* __restrict__
     // rows of policies without a played cell, duplicates) goes on with the fp64
     // maxima.  us per 1000 iterations, tied throughout: 428 at P = 128 with the
     // high words, 296 like this; 292 and 214 at P = 64.
+    // With four policies per lane fp64 maxima are faster anyway (P = 256, no ties:
+    // 535 us against 574).
     int t = 0, ties = 0;
-    for (; t < T; ++t) {
+    for (; K < 4 && t < T; ++t) {
         extremes();
         if (__builtin_expect(tied(), 0)) {
             if (8 * ++ties > t + 64)
