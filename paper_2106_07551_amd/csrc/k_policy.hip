@@ -434,7 +434,8 @@ struct MlpBf16Args {
 // the base address and size sit in scalar registers, each load takes the
 // lane's byte offset (lane * 16, one VGPR for all loads) and the fragment's
 // wave-uniform byte offset in a scalar register, so no 64-bit per-lane
-// addresses are kept.  Loads beyond n_frags fragments return zero.
+// addresses are kept.  (Every idx is below n_frags: the resource's range check
+// does not cover the scalar offset.)
 using Frags = __amdgpu_buffer_rsrc_t;
 
 __device__ __forceinline__ Frags frag_src(const uint4* base, int n_frags)
@@ -1124,7 +1125,7 @@ __device__ __forceinline__ void generic_load(GenericW<BF16, NI>& w, __amdgpu_buf
 {
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
-        const int blk = (nt0 + 8 * i) * kgs + g;   // past the end: zeros
+        const int blk = (nt0 + 8 * i) * kgs + g;   // g < kgs: inside the layer
         if constexpr (BF16) {
             const auto v = __builtin_amdgcn_raw_buffer_load_b64(src, lane * 8, blk * 512, 0);
             w.h[i] = make_uint2(v[0], v[1]);
