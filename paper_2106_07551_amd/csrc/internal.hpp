@@ -333,15 +333,22 @@ struct FiniteLaunch {
     // batch with finite_adds; null otherwise
     unsigned long long *sum, *sumsq, *cnt;
 };
-// Whether a batch's envs add to the table by themselves (one set of atomics per
-// env, or per wavefront of one pair): where the payoff kernels would need the
-// slots sorted by policy (P > 64), and where few envs share a cell (pursuit, 10
-// steps: P = 100, 16384 envs 106 -> 68 us a fill, 131072 envs 129 -> 89; P = 64,
-// 16384 envs 67 -> 63, 65536 envs 69 -> 74; P = 32, 8192 envs 57 -> 55, 32768
-// envs 56 -> 63 us).
+// Whether a batch's envs add to the table by themselves (combined by workgroup, one
+// set of atomics per cell that a workgroup touches): where the payoff kernels would
+// need the slots sorted by policy (P > 64), and where few envs share a cell, unless
+// the batch is so large that the atomics could queue up on a few lines of the table
+// (12 ns each).  us a fill with another kernel -> like this, ids drawn uniformly /
+// from two policies / from eight neighbouring ones (the worst case, one line for
+// every eight cells): one-step games, P = 64, 8192 envs 16 / 16 / 15 -> 12 / 12 / 13,
+// 16384 envs 16 / 16 / 15 -> 13 / 12 / 18, 32768 envs 17 / 16 / 15 -> 15 / 13 / 28;
+// pursuit of 10 steps, P = 64, 16384 envs 42 / 39 / 39 -> 37 / 33 / 35; P = 16, 16384
+// envs 39 / 38 / 38 -> 36 / 34 / 34; with the slots sorted, P = 100, 65536 envs
+// 276 / 265 / 262 -> 40 / 35 / 56.
+constexpr int kFiniteAddsMax = 16384;
 inline bool finite_adds(int64_t n_envs, int P)
 {
-    return P * P > kPayoffStreamMaxCells || n_envs <= 8 * (int64_t)P * P;
+    return P * P > kPayoffStreamMaxCells ||
+           n_envs <= std::min<int64_t>(8 * (int64_t)P * P, kFiniteAddsMax);
 }
 hipError_t launch_finite(const FiniteLaunch& L, hipStream_t s);
 hipError_t launch_finite_logits(const FiniteLaunch& L, float* out, hipStream_t s);

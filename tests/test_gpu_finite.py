@@ -232,3 +232,46 @@ def test_envs_add_to_the_table(P, n, swap):
     bad = run_gpu(wl, trace=False, check=False, pairs=pairs)["table"]
     assert bad["status"] == M.binding.E_DEVICE and bad["device_flags"] == 1
     assert bad["counts"].sum() == n - 1
+
+
+def _fill_us(wl, pairs, reps=9):
+    """The fill's time on the GPU (the fastest of `reps`)."""
+    from paper_2106_07551_amd import workload_io as IO
+    env, pop = IO.make_env(wl), IO.make_population(wl)
+    pt = torch.from_numpy(np.ascontiguousarray(pairs, dtype=np.int32)).cuda()
+    us = []
+    for _ in range(reps):
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record()
+        pop.rollout(env, len(pairs), pt, wl.seed, wl.horizon)
+        b.record()
+        torch.cuda.synchronize()
+        us.append(1000 * a.elapsed_time(b))
+    pop.close()
+    return min(us)
+
+
+@pytest.mark.parametrize("P,n", [(64, 16384), (100, 65536)])
+def test_a_sparse_meta_strategy_costs_no_more(P, n):
+    """Envs that share four cells of the table do not queue up for them: with one
+    set of atomics per env these fills took 6 and 13 times those of ids drawn from
+    all policies, now they take less."""
+    wl = dataclasses.replace(W.make(1, P=P, per_pair=1, horizon=1), n_envs=n)
+    spread, two = W.random_pairs(P, n, 2), W.random_pairs(2, n, 2) * (P // 2)
+    a, b = _fill_us(wl, spread), _fill_us(wl, two)
+    say(f"[finite] P={P} n={n}: all policies {a:.1f} us, two of them {b:.1f} us")
+    assert b <= 3 * a
+
+
+@pytest.mark.parametrize("n", [1, 7, 8, 9, 127, 128, 129, 4097, 16384, 16385])
+@pytest.mark.parametrize("support", [1, 2, 9, 64])
+def test_workgroups_combine_their_cells(n, support):
+    """Few and many cells per workgroup at each number of lanes per env, and the
+    largest batch whose envs add by themselves: the table is exactly the returns'."""
+    import oracle
+    wl = W.with_policies(W.make(3, P=64, n_envs=n, horizon=17), W.MLP_BF16, [75, 64, 64, 5])
+    pairs = W.random_pairs(support, n, 2) * (63 // support)
+    g = run_gpu(wl, trace=False, pairs=pairs)
+    mean, cnt, _, _ = oracle.payoff(g["returns"], pairs, wl.team, 64)
+    assert np.array_equal(g["table"]["counts"], cnt)
+    assert np.abs(g["table"]["mean"] - mean)[cnt > 0].max() <= 1e-9
