@@ -349,24 +349,35 @@ __global__ __launch_bounds__(64) void solve_fp_kernel(const double* __restrict__
         }
     };
     // A game whose extremes tie in more than an eighth of the iterations (equal
-    // rows of policies without a played cell, duplicates) goes on with the fp64
-    // maxima.  us per 1000 iterations, tied throughout: 428 at P = 128 with the
-    // high words, 296 like this; 292 and 214 at P = 64.
+    // rows of policies without a played cell, duplicates) goes on with fp64 maxima,
+    // from the third tied iteration at the earliest (all sums tie in the first).
+    // us per 1000 iterations, tied throughout: 428 at P = 128 with the high words,
+    // 295 like this, 303 with fp64 maxima from the start; P = 64 292, 208 and 209.
     // With four policies per lane fp64 maxima are faster anyway (P = 256, no ties:
     // 535 us against 574).
     int t = 0, ties = 0;
     for (; K < 4 && t < T; ++t) {
         extremes();
         if (__builtin_expect(tied(), 0)) {
-            if (8 * ++ties > t + 64)
+            if (8 * ++ties > t + 16)
                 break;   // this iteration is played below
             low_words();
         }
         play(first(bi), first(bj));
     }
     for (; t < T; ++t) {
-        extremes_f64();
-        play(first(bi), first(bj));
+        if constexpr (K == 1) {
+            // one policy per lane: from the two values, without the masks (which
+            // took 214 instead of 209 us per 1000 iterations at P = 64)
+            double vi = v[0], wj = w[0];
+            wave_max_min(vi, wj);
+            const unsigned long long mi = __ballot(v[0] == vi), mj = __ballot(w[0] == wj);
+            const int i = mi ? __ffsll(mi) - 1 : P - 1, j = mj ? __ffsll(mj) - 1 : P - 1;
+            play(min(i, P - 1), min(j, P - 1));
+        } else {
+            extremes_f64();
+            play(first(bi), first(bj));
+        }
     }
 #pragma unroll
     for (int q = 0; q < K; ++q) {

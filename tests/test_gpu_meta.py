@@ -324,3 +324,13 @@ def test_solve_fp_ties_of_unplayed_policies(P):
         _check_solve(M, 200)
         # all payoffs beside one value, a few of them off by its last bits
         _check_solve(np.where(rng.random((P, P)) < 0.02, 2.0 ** -50, 0.0) + 0.5, 200)
+
+
+@pytest.mark.parametrize("P", [1, 2, 5, 17, 63, 64, 65, 128])
+@pytest.mark.parametrize("T", [1, 2, 3, 4, 60, 700])
+def test_solve_fp_ties_now_and_then(P, T):
+    """Small integer payoffs tie at irregular steps, so the change to fp64 maxima
+    falls on any of them (or on none); the sums are exact and so are the ties."""
+    rng = np.random.default_rng([960, P, T])
+    for span in (1, 4, 40):
+        _check_solve(rng.integers(-span, span + 1, size=(P, P)).astype(np.float64), T)
