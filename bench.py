@@ -442,7 +442,12 @@ def bandwidth_sweep(factors, horizon):
             work = algorithmic_work(wl)
             for kname, k in (("env", M.K_ENV), ("payoff", M.K_PAYOFF)):
                 ms, cnt = pop.profile_read(k)
-                avg_us = 1000.0 * ms / max(cnt, 1)
+                if cnt == 0:      # short games: inside the env kernel
+                    print(json.dumps({"bandwidth_sweep": name, "kernel": kname, "scale": f,
+                                      "n_envs": n, "slots": n * na, "launches": 0,
+                                      "fused_into": "env"}), flush=True)
+                    continue
+                avg_us = 1000.0 * ms / cnt
                 b = work[kname]["bytes"]
                 gbs = b / (avg_us * 1e-6) / 1e9
                 row = {"bandwidth_sweep": name, "kernel": kname, "scale": f, "n_envs": n,
@@ -578,6 +583,8 @@ def main():
         kern[name] = {"total_ms": round(ms, 3), "launches": cnt,
                       "avg_us": round(1000.0 * ms / max(cnt, 1), 3),
                       "per_step_us" if per > 1 else "per_fill_us": round(1000.0 * ms / per, 3)}
+        if name == "payoff" and cnt == 0:      # short games: inside the env kernel
+            kern[name]["fused_into"] = "env"
         if name in work and cnt:
             t = ms * 1e-3 / per
             w = work[name]

@@ -541,9 +541,11 @@ enum {
     MALIB_K_SAMPLE = 1,   /* Gumbel-max action sampling: runs inside the env
                              step (MALIB_K_ENV), so this class records no
                              launches */
-    MALIB_K_ENV = 2,      /* environment step + return accumulation */
+    MALIB_K_ENV = 2,      /* environment step + return accumulation; games with few
+                             distinct observations: the whole horizon */
     MALIB_K_SETUP = 3,    /* bucketing + reset */
-    MALIB_K_PAYOFF = 4,   /* payoff reduction */
+    MALIB_K_PAYOFF = 4,   /* payoff reduction (no launch where the horizon's kernel
+                             adds the envs to the table itself) */
     MALIB_K_COUNT = 5
 };
 

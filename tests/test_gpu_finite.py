@@ -275,3 +275,18 @@ def test_workgroups_combine_their_cells(n, support):
     mean, cnt, _, _ = oracle.payoff(g["returns"], pairs, wl.team, 64)
     assert np.array_equal(g["table"]["counts"], cnt)
     assert np.abs(g["table"]["mean"] - mean)[cnt > 0].max() <= 1e-9
+
+
+@pytest.mark.parametrize("n,launches", [(8192, 0), (16385, 1)])
+def test_profile_counts_no_payoff_launch_where_the_envs_add(n, launches):
+    import paper_2106_07551_amd as M
+    from paper_2106_07551_amd import workload_io as IO
+    wl = dataclasses.replace(W.make(1, P=64, per_pair=1, horizon=1), n_envs=n)
+    env, pop = IO.make_env(wl), IO.make_population(wl)
+    pt = torch.from_numpy(W.random_pairs(64, n, 2)).cuda()
+    pop.profile_enable(True)
+    pop.rollout(env, n, pt, wl.seed, 1)
+    assert pop.profile_read(M.K_ENV)[1] == 1
+    assert pop.profile_read(M.K_PAYOFF)[1] == launches
+    assert pop.payoff()["counts"].sum() == n
+    pop.close()
