@@ -60,7 +60,7 @@ enum {
  * environment variable MALIB_FAULT_ALLOC is set to anything but "" or "0",
  * every device or pinned host allocation the library makes (handle creation
  * and extension, growth of a handle's batch buffers, the meta-samplers'
- * thresholds) fails without allocating and the call returns MALIB_E_NOMEM,
+ * thresholds where they need a buffer) fails without allocating and the call returns MALIB_E_NOMEM,
  * leaving handles as they were.  The variable is read at each allocation.
  */
 

@@ -1364,11 +1364,7 @@ malib_status malib_meta_sample(const float* sigma, int32_t n_sigma, int32_t P, i
     if (n_envs == 0)
         return MALIB_OK;
     hipStream_t s = (hipStream_t)stream;
-    if ((int)thr.size() <= kMaxThresholdArgs) {
-        // nothing to allocate; the allocation fault hook fails this call all the
-        // same, so that a caller's handling of E_NOMEM here can be tested
-        if (fault_alloc())
-            HIP_TRY(hipErrorOutOfMemory);
+    if ((int)thr.size() <= kMaxThresholdArgs) {   // nothing to allocate
         HIP_TRY(launch_meta_sample_args(thr.data(), (int)thr.size(), default_seat_map(n_sigma), P,
                                         n_envs, n_agents, seed, env_offset, out, s));
         return MALIB_OK;

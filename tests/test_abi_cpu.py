@@ -182,18 +182,21 @@ def test_policy_ids_validated_before_device_work():
 
 def test_fault_hook_forces_nomem(monkeypatch):
     """MALIB_FAULT_ALLOC makes the library's allocations fail as out of memory
-    (here the meta-sampler's threshold buffer, reached after validation with no
-    device work before it); cleared, the same call gets past the hook."""
+    (here the meta-sampler's threshold buffer, which more than 448 thresholds
+    need, reached after validation with no device work before it); cleared, the
+    same call gets past the hook, and so does one that allocates nothing."""
     import paper_2106_07551_amd as M
     L = M.lib()
     B = M.binding
-    sig = np.array([1.0, 2.0, 3.0], np.float32)
+    sig = np.arange(1, 451, dtype=np.float32)   # two seats' rows of 225
     out = C.c_void_p(16)   # never dereferenced: the allocation fails first
     monkeypatch.setenv("MALIB_FAULT_ALLOC", "1")
-    assert L.malib_meta_sample(sig.ctypes.data, 1, 3, 10, 2, 1, 0, out, None) == B.E_NOMEM
-    assert b"out of memory" in L.malib_last_error().lower() or b"dev_malloc_async" in \
-        L.malib_last_error()
-    monkeypatch.setenv("MALIB_FAULT_ALLOC", "0")
-    # without the hook the call reaches the HIP runtime (no GPU here: a HIP error)
-    st = L.malib_meta_sample(sig.ctypes.data, 1, 3, 10, 2, 1, 0, out, None)
-    assert st != B.E_NOMEM and st != B.E_INVAL
+    assert L.malib_meta_sample(sig.ctypes.data, 2, 225, 10, 2, 1, 0, out, None) == B.E_NOMEM
+    assert b"dev_malloc_async" in L.malib_last_error()
+    if not os.path.exists("/dev/kfd"):   # (on a GPU these calls would write to `out`)
+        st = L.malib_meta_sample(sig.ctypes.data, 2, 224, 10, 2, 1, 0, out, None)
+        assert st != B.E_NOMEM and st != B.E_INVAL
+        monkeypatch.setenv("MALIB_FAULT_ALLOC", "0")
+        # without the hook the call reaches the HIP runtime (no GPU here: a HIP error)
+        st = L.malib_meta_sample(sig.ctypes.data, 2, 225, 10, 2, 1, 0, out, None)
+        assert st != B.E_NOMEM and st != B.E_INVAL
