@@ -542,9 +542,10 @@ hipError_t launch_finite(const FiniteLaunch& L, hipStream_t s)
     const int64_t n = L.n_envs;
     const int H = L.t1 - L.t0;
     // lanes per env: the noise of more steps at once where the batch leaves the
-    // chip idle (pursuit, 100 steps: 1040 envs 37 / 51 / 82 us with 32 / 8 / 2,
-    // 16384 envs 109 / 68 / 83 us, 32768 envs 194 / 114 / 88 us)
-    int nl = n <= 4096 ? 32 : n <= 24576 ? 8 : 2;
+    // chip idle, by envs per CU (256 CUs, pursuit, 100 steps: 1040 envs 37 / 51 / 82
+    // us with 32 / 8 / 2, 16384 envs 109 / 68 / 83 us, 32768 envs 194 / 114 / 88 us)
+    const int64_t cus = e.n_cus > 0 ? e.n_cus : 256;
+    int nl = n <= 16 * cus ? 32 : n <= 96 * cus ? 8 : 2;
     if (e.A > 8)
         nl = 2;
     while (nl > 2 && nl / 2 > H)
