@@ -873,11 +873,13 @@ static malib_status handle_bufs(malib_pop_t pop, const malib_env_desc* env, int6
     return MALIB_OK;
 }
 
-// The launch sequence of one batch on buffers `b`: set-up (returns cleared,
-// bucketing, reset), `horizon` steps of policy forward -> env step (sampling
-// inside), then the payoff reduction into the handle's table.  `snap_of`
-// (host, [horizon], or NULL) maps a step to its trace snapshot; `prof`
-// enables the handle's HIP-event timing.
+// The launch sequence of one batch on buffers `b`, then the payoff reduction into
+// the handle's table.  Games with few distinct observations (plan.finite): the
+// policies' logits on all of them, then the whole horizon in one launch (one per
+// stretch between trace snapshots), which may add the envs to the table itself.
+// Else: set-up (returns cleared, bucketing, reset) and `horizon` steps of policy
+// forward -> env step (sampling inside).  `snap_of` (host, [horizon], or NULL)
+// maps a step to its trace snapshot; `prof` enables the handle's HIP-event timing.
 static malib_status launch_rollout(malib_pop_t pop, const malib_env_desc* env, int64_t n_envs,
                                    const int32_t* pair_assign, uint64_t seed,
                                    int64_t env_offset, int32_t horizon, float* returns,

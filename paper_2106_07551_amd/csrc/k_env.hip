@@ -260,8 +260,8 @@ __global__ __launch_bounds__(256) void step_pursuit_kernel(
 // ------------------------------------------------------------ feature dynamics
 
 // GW consecutive floats (GW = 1, 2 or 4) as one load or store: outputs are
-// mapped to threads in groups of GW consecutive indices, so the WT reads from
-// LDS, the embedding loads and the state stores are single wide accesses.
+// mapped to threads in groups of GW consecutive indices, so the accumulator rows
+// in LDS, the embedding loads and the state stores are single wide accesses.
 template <int GW>
 struct FVec;
 template <>
@@ -360,6 +360,8 @@ struct FeatTile {
     static constexpr int Q4 = D / 4;
     static constexpr int SQ = E * Q4 / (64 * WAVES);   // state float4s per thread
     static_assert(NTW * WAVES * 16 == D && EPW * WAVES == E && SQ * 64 * WAVES == E * Q4, "split");
+    static_assert(EPW * kMaxAgents <= 64, "an epilogue wavefront takes its envs' given actions "
+                                          "with one lane per slot");
 };
 
 typedef float v4f_t __attribute__((ext_vector_type(4)));
@@ -523,7 +525,7 @@ __device__ __forceinline__ void feat_actions(const FeatArgs& f, int64_t e0, int 
         act[(el - ew * T::EPW) * kMaxAgents + seat] = (uint8_t)a;
     };
     if (sa.actions) {
-        if (tx < slots) {   // at most 4 envs x 8 seats
+        if (tx < slots) {   // one lane per slot
             const int el = ew * T::EPW + tx / ea.n_agents;
             put(tx, el, e0 + el, given);
         }

@@ -13,7 +13,7 @@
 // cycles, per slot and step), small ones by the steps' latency.  2^20 envs of the
 // iterated game, 32 steps: 32 x (265 + 17) us before, now 25 us for the table's
 // 118096 rows and 400 us; pursuit, 16384 envs, 100 steps: 100 x (12 + 5) us
-// before, now 8 + 60 us.
+// before, now 8 + 68 us.
 #include "device.hpp"
 #include "internal.hpp"
 
