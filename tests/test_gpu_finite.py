@@ -70,6 +70,20 @@ def _policies(wl, P):
                                biases=[b[pick] for b in wl.biases])
 
 
+def _env_launches(wl, pairs):
+    """Launches of the env kernel in an untraced batch: one for the horizon kernel,
+    one a step on the step-by-step route."""
+    import paper_2106_07551_amd as M
+    from paper_2106_07551_amd import workload_io as IO
+    env, pop = IO.make_env(wl), IO.make_population(wl)
+    pt = torch.from_numpy(np.ascontiguousarray(pairs, dtype=np.int32)).cuda()
+    pop.profile_enable(True)
+    pop.rollout(env, len(pairs), pt, wl.seed, wl.horizon)
+    n = pop.profile_read(M.K_ENV)[1]
+    pop.close()
+    return n
+
+
 @pytest.mark.parametrize("horizon", [2, 5, 9])
 @pytest.mark.parametrize("actions", [1, 2])
 def test_iter_fewer_actions(actions, horizon):
@@ -78,8 +92,11 @@ def test_iter_fewer_actions(actions, horizon):
     base = W.make(2, P=3, per_pair=1, horizon=horizon)
     wl = dataclasses.replace(base, n_actions=actions, n_envs=70,
                              A=np.ascontiguousarray(base.A[-actions:, -actions:]))
-    wl = W.with_policies(wl, W.MLP_F32, [8 * actions, 512, 500, actions], bias_var=0.05)
+    wl = W.with_policies(wl, W.MLP_F32, [8 * actions, 700, 699, actions], bias_var=0.05)
     pairs = W.random_pairs(3, 70, 2)
+    assert _env_launches(wl, pairs) == 1
+    if actions == 2:
+        assert _env_launches(_policies(wl, 256), pairs) == horizon
     a = run_gpu(wl, trace=False, pairs=pairs)
     _same(a, run_gpu(wl, snaps=[0, horizon - 1], pairs=pairs))
     b = run_gpu(_policies(wl, 256), trace=False, pairs=pairs)
@@ -113,9 +130,9 @@ ROUTES = {
                                                   W.MLP_F32, [24, 40, 30, 3], bias_var=0.05),
     "iter_bf16": lambda n: W.with_policies(W.make(2, P=3, per_pair=1, horizon=5), W.MLP_BF16,
                                            [24, 64, 64, 3], bias_var=0.05),
-    "pursuit_bf16": lambda n: W.with_policies(W.make(3, P=3, n_envs=n, horizon=5), W.MLP_BF16,
+    "pursuit_bf16": lambda n: W.with_policies(W.make(3, P=3, n_envs=n, horizon=3), W.MLP_BF16,
                                               [75, 256, 256, 5], bias_var=0.05),
-    "pursuit_f32": lambda n: W.with_policies(W.make(3, P=3, n_envs=n, horizon=4), W.MLP_F32,
+    "pursuit_f32": lambda n: W.with_policies(W.make(3, P=3, n_envs=n, horizon=3), W.MLP_F32,
                                              [75, 256, 256, 5], bias_var=0.05),
 }
 
@@ -129,6 +146,8 @@ def test_table_equals_step_by_step(name, n):
     pairs = W.random_pairs(3, n, 2)
     a = run_gpu(wl, trace=False, pairs=pairs)
     big = _policies(wl, 256)
+    assert _env_launches(wl, pairs) == 1
+    assert _env_launches(big, pairs) == wl.horizon
     b = run_gpu(big, snaps=[0, wl.horizon - 1], pairs=pairs)
     say(f"[finite] {name} n={n}")
     assert np.array_equal(a["returns"].view(np.uint32), b["returns"].view(np.uint32))
@@ -152,7 +171,7 @@ def test_nan_and_bad_ids_are_flagged_without_a_trace():
         assert t["status"] == M.binding.E_DEVICE and t["device_flags"] == 1
 
 
-@pytest.mark.parametrize("warm,played", [(60, 5), (5, 60), (1, 60), (60, 1)])
+@pytest.mark.parametrize("warm,played", [(100, 5), (5, 100), (1, 100), (100, 1)])
 def test_capture_after_a_batch_of_another_horizon(warm, played):
     """A batch outside the capture leaves room for one of the same size inside,
     whichever of the two ways each of them takes."""
@@ -160,7 +179,10 @@ def test_capture_after_a_batch_of_another_horizon(warm, played):
     wl = _policies(W.make(2, P=3, per_pair=1), 256)
     n = 60
     env = IO.make_env(wl)
-    pt = torch.from_numpy(W.random_pairs(256, n, 2)).cuda()
+    pairs = W.random_pairs(256, n, 2)
+    for horizon, launches in ((100, 1), (5, 5), (1, 1)):
+        assert _env_launches(dataclasses.replace(wl, horizon=horizon), pairs) == launches
+    pt = torch.from_numpy(pairs).cuda()
     ref, ret = (torch.empty((2, n), dtype=torch.float32, device="cuda") for _ in range(2))
     eager, pop = IO.make_population(wl), IO.make_population(wl)
     eager.rollout(env, n, pt, wl.seed, played, returns=ref)
