@@ -809,7 +809,7 @@ __device__ __forceinline__ void build_obs(const MlpBf16Args& a, const int* row_s
                 // conditional load here made the compiler spill
                 const int env = row_env[r0 + (u0 + u) * ROWS_PER_PASS];
                 const uint4 t =
-                    *reinterpret_cast<const uint4*>(S + (uint32_t)max(env, 0) * (uint32_t)KIN);
+                    *reinterpret_cast<const uint4*>(S + (int64_t)max(env, 0) * KIN);
                 v[u] = env >= 0 ? t : make_uint4(0, 0, 0, 0);
             }
 #pragma unroll
@@ -1476,7 +1476,7 @@ __global__ __launch_bounds__(512, 1) void mlp_bf16_persist_kernel(MlpBf16Args a)
             const int env = row_env[0][orow + u * RPP];
             ob[u] = v4f{0.f, 0.f, 0.f, 0.f};
             if (env >= 0)
-                ob[u] = *reinterpret_cast<const v4f*>(S0 + (uint32_t)env * (uint32_t)KIN);
+                ob[u] = *reinterpret_cast<const v4f*>(S0 + (int64_t)env * KIN);
         }
 #pragma unroll
         for (int u = 0; u < PASSES; ++u)
@@ -1552,7 +1552,7 @@ __global__ __launch_bounds__(512, 1) void mlp_bf16_persist_kernel(MlpBf16Args a)
                 const int env = row_env[cur ^ 1][orow + u * RPP];
                 ob[u] = v4f{0.f, 0.f, 0.f, 0.f};
                 if (env >= 0)
-                    ob[u] = *reinterpret_cast<const v4f*>(S0 + (uint32_t)env * (uint32_t)KIN);
+                    ob[u] = *reinterpret_cast<const v4f*>(S0 + (int64_t)env * KIN);
             }
         }
         __syncthreads();
@@ -1575,7 +1575,7 @@ __global__ __launch_bounds__(512, 1) void mlp_bf16_persist_kernel(MlpBf16Args a)
                 const int env = row_env[cur ^ 1][orow + (u0 + u) * RPP];
                 o2[u] = v4f{0.f, 0.f, 0.f, 0.f};
                 if (env >= 0)
-                    o2[u] = *reinterpret_cast<const v4f*>(S0 + (uint32_t)env * (uint32_t)KIN);
+                    o2[u] = *reinterpret_cast<const v4f*>(S0 + (int64_t)env * KIN);
             }
 #pragma unroll
             for (int u = 0; u < PRE; ++u)

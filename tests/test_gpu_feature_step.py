@@ -56,3 +56,27 @@ def test_step_subnormal_sums(d, n):
     s1 = np.abs(g["states"][1])
     assert ((s1 > 0) & (s1 < np.finfo(np.float32).tiny)).mean() > 0.9
     check_parity(wl, g, np.arange(n) if n < 64 else _edges(n, np.random.default_rng(1)))
+
+
+@pytest.mark.parametrize("d,n", [(256, 2 ** 24), (512, 2 ** 23)])
+def test_observation_rows_past_2_32_elements(d, n):
+    """The last envs of a batch whose states hold more than 2^32 values play as
+    they do in a small batch at their offset (64-row and persistent forward)."""
+    from paper_2106_07551_amd import workload_io as IO
+    if torch.cuda.mem_get_info()[0] < 80 << 30:
+        pytest.skip("needs 80 GB")
+    extra = 1500
+    wl = W.team_variant(2, d=d, P=2, n_envs=extra, horizon=2)
+    wl = W.with_policies(wl, W.MLP_BF16, [d, 64, 64, 18])
+    env, pop = IO.make_env(wl), IO.make_population(wl)
+    g = torch.Generator(device="cuda").manual_seed(d)
+    pairs = torch.randint(0, 2, (n + extra, 2), generator=g, device="cuda", dtype=torch.int32)
+    ref = torch.empty((2, extra), device="cuda")
+    pop.rollout(env, extra, pairs[n:].contiguous(), wl.seed, 2, env_offset=n, returns=ref)
+    ret = torch.empty((2, n + extra), device="cuda")
+    say(f"[step] d={d} n={n + extra}")
+    pop.rollout(env, n + extra, pairs, wl.seed, 2, returns=ret)
+    torch.cuda.synchronize()
+    pop.close()
+    assert torch.unique(ref).numel() > extra
+    assert torch.equal(ret[:, n:], ref)
