@@ -419,13 +419,15 @@ malib_status malib_solve_fp(const double* M, int32_t n_policies, int32_t iterati
  * PSRO experiments, Sec. 4.2): the exact equilibrium of the two-player
  * zero-sum game M (the row side receives M[i][j], the column side -M[i][j]),
  * its value v = max_x min_j (x^T M)_j = min_y max_i (M y)_i, by the primal
- * simplex method (Bland's rule, fp64) on the column side's problem after
+ * simplex method (fp64; the most negative reduced cost enters, Bland's rule
+ * after 8 degenerate pivots in a row) on the column side's problem after
  * shifting M to positive entries; the row side's strategy is the dual
  * solution.  Optimal strategies need not be unique; the value is.
  *  M:      device fp64 [P][P], finite (a NaN or infinite entry gives NaN
  *          value, x, y and sigma, and pivots = -1).
- *  work:   device fp64 [P+1][2P+1] workspace, needed for P > 96 (NULL
- *          allowed below: the tableau then lives in registers).
+ *  work:   device fp64 [P+1][2P+1] workspace, required for P > 96 (NULL
+ *          allowed up to there).  Up to P = 224 the tableau lives in
+ *          registers and the workspace is not touched.
  *  value:  device fp64 [1]; x, y: device fp64 [P] (row and column side).
  *  sigma:  device fp32 [2][P] or NULL: x and y as weight rows for
  *          malib_meta_sample_device.

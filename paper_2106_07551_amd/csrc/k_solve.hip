@@ -808,7 +808,7 @@ hipError_t launch_alpharank(const double* M, int P, double alpha, int m, double*
 // row in LDS and updates the other rows.
 
 constexpr int kLpThreads = 1024;
-constexpr int kLpWorkAbove = 96;   // callers give a workspace above this
+constexpr int kLpWorkAbove = 96;   // callers give a workspace above this (used above kLpRegMax)
 constexpr double kLpEps = 1e-11;
 constexpr int kLpDegenerate = 8;
 
