@@ -1,9 +1,9 @@
 """alpha-rank on the GPU (malib_solve_alpharank, through the C ABI) against
 the oracle's definition (oracle.alpharank: the stationary distribution of the
 alpha-rank chain by a dense linear solve), on random games from 1 to 256
-policies (LDS path up to 128, workspace path above), several ranking
-intensities and population sizes, a symmetric game, alpha = 0, and the game
-of a real 4v4 table.  Tolerance: |pi_gpu - pi_oracle| <= 1e-12 + 1e-9 pi (both
+policies (registers up to 224, workspace above), several ranking intensities
+and population sizes, a symmetric game, alpha = 0, and the game of a real 4v4
+table.  Tolerance: |pi_gpu - pi_oracle| <= 1e-12 + 1e-9 pi (both
 sides are fp64; the elimination orders differ, and the oracle's solve is
 accurate to rounding of the largest component)."""
 import numpy as np

@@ -3,8 +3,8 @@ the oracle's LPs (scipy's HiGHS): the value within 1e-9 (relative to the
 payoff scale), and the GPU's own strategies checked for what makes them
 optimal, since optimal strategies need not be unique: distributions, and
 min_j (x^T M)_j >= v - 1e-9, max_i (M y)_i <= v + 1e-9.  Games of 1 to 256
-policies (LDS tableau up to 96, workspace above), a degenerate game with many
-ties, rock-paper-scissors, and the game of a real 4v4 table."""
+policies (tableau in registers up to 224, workspace above), a degenerate game
+with many ties, rock-paper-scissors, and the game of a real 4v4 table."""
 import numpy as np
 import pytest
 
@@ -77,11 +77,11 @@ def test_lp_on_a_4v4_table():
 
 
 @pytest.mark.parametrize("bad", [float("nan"), float("inf"), -float("inf")])
-@pytest.mark.parametrize("P", [3, 120])
+@pytest.mark.parametrize("P", [3, 120, 225])
 def test_lp_non_finite_game_gives_nan(bad, P):
     """A NaN or infinite payoff leaves no game to solve: value, both
     strategies and the weight rows are NaN and pivots is -1, for the tableau
-    in LDS (P <= 96) and in the workspace."""
+    in registers (P <= 224) and in the workspace."""
     import paper_2106_07551_amd as MA
     M = np.random.default_rng(P).uniform(-1, 1, (P, P))
     M[P // 2, P - 1] = bad
